@@ -215,6 +215,11 @@ EvalBufs eval_bufs_ctx(Ctx &c, int64_t n) {
     b.order = c.tile_order.as<int32_t>();
     b.sort_tmp = c.sort_tmp.p;
     b.sort_bytes = tb;
+    b.part = nullptr;
+    if (c.opt.far_field == LSS_FAR_DIRECT) {
+        c.part.ensure(direct_part_bytes(c, n));
+        b.part = c.part.p;
+    }
     b.pairs = c.pairs.as<double>();
     b.n_dev = nullptr;
     return b;
@@ -249,7 +254,8 @@ void eval_direct_bufs(Ctx &c, const EvalBufs &b, const double *x, const int32_t 
         LSS_HIP(hipMemsetAsync(b.pairs, 0, 4 * sizeof(double), c.stream));
         c.ev_begin();
     }
-    launch_p2p_direct(c, n, b.n_dev, b.tx, b.ty, b.tz, b.tmesh, b.perm2, phi, grad, 3, b.pairs);
+    launch_p2p_direct(c, n, b.n_dev, b.tx, b.ty, b.tz, b.tmesh, b.perm2, phi, grad, 3, b.pairs,
+                      b.part);
     if (b.pairs) c.ev_end();
 }
 
@@ -327,7 +333,7 @@ void newton_iteration(Ctx &c, int64_t N, double tau, double *phi, double *grad) 
                         c.tile_order.as<int32_t>(), c.pairs.as<double>());
     } else {
         launch_p2p_direct(c, N, nact, c.tx.as<double>(), c.ty.as<double>(), c.tz.as<double>(), c.tmesh.as<int32_t>(),
-                          nullptr, phi, grad, 3, c.pairs.as<double>());
+                          nullptr, phi, grad, 3, c.pairs.as<double>(), c.part.p);
     }
     launch_newton_update(c, N, tau, phi, grad);
     launch_compact_active(c, N);
@@ -377,7 +383,7 @@ std::vector<uint64_t> newton_key(const Ctx &c, int64_t N, double tau, int maxit,
     const DBuf *bufs[] = {&s.T, &s.H, &s.h, &s.lo, &s.hi, &s.sig, &s.mesh, &s.orig, &s.status, &s.iters, &s.seen,
                           &s.active, &s.active2, &s.flag, &s.blocksum, &s.nact, &s.hist, &s.phi, &s.grad,
                           &c.tx, &c.ty, &c.tz, &c.tmesh, &c.tleaf, &c.tstart, &c.ntiles, &c.tflag, &c.tpos,
-                          &c.tile_order, &c.tile_bucket, &c.tile_queue, &c.pairs, &c.src, &c.node_off, &c.verts,
+                          &c.tile_order, &c.tile_bucket, &c.tile_queue, &c.part, &c.pairs, &c.src, &c.node_off, &c.verts,
                           &c.tris, &c.vH, &c.sigma, &c.tri_off, &t.p2p_beg, &t.p2p_end, &t.p2p_val2, &t.nb, &t.ne,
                           &t.level, &t.ijk, &t.src, &t.L, &t.M, &t.m2p_beg, &t.m2p_end, &t.m2p_val2, &t.root,
                           &t.bmesh, &t.child, &t.parent, &t.rmax, &t.near_cnt};
@@ -405,6 +411,7 @@ void project(Ctx &c, const double *uv, int32_t np, double *h, double *xout, int8
     launch_chart_init(c, duv.as<double>(), np, N);
     ensure_targets(c, N);
     if (c.opt.far_field == LSS_FAR_FMM) ensure_tiles(c, N);
+    else c.part.ensure(direct_part_bytes(c, N));
     NewtonState &s = c.ns;
     DBuf &phi = s.phi, &grad = s.grad;
     phi.ensure(sizeof(double) * N);

@@ -275,6 +275,7 @@ struct Ctx {
     DBuf tkey, tkey2, tperm, tperm2, tx, ty, tz, tmesh, sort_tmp;
     DBuf tflag, tpos, tstart, ntiles, tleaf;   // FMM eval: leaf of each sorted target, tile heads
     DBuf pairs;               // double accumulator of executed pairs (stats)
+    DBuf part;                // partial sums of a direct evaluation whose nodes are split
     DBuf tile_queue;          // uint32[2] work queue of the FMM evaluation (zero between launches)
     DBuf tile_order;          // FMM tiles, most expensive first (int32 per tile)
     DBuf tile_bucket;         // int32[2 * kCostBuckets]: bucket counts (zero between uses), offsets
@@ -337,10 +338,13 @@ void launch_target_keys(Ctx &c, const double *x, const int32_t *x_mesh, int64_t 
 void launch_gather_targets(Ctx &c, const double *x, const int32_t *x_mesh, const int32_t *perm,
                            int64_t n, double *tx, double *ty, double *tz, int32_t *tmesh);
 
-// pair kernels (lss_p2p.hip); pairs: the statistics counters (null: none)
+// pair kernels (lss_p2p.hip); pairs: the statistics counters (null: none);
+// part: direct_part_bytes of workspace (null: the node range is not split)
+int direct_splits(const Ctx &c, int64_t n);
+size_t direct_part_bytes(const Ctx &c, int64_t n);
 void launch_p2p_direct(Ctx &c, int64_t n, const int32_t *n_dev, const double *tx, const double *ty,
                        const double *tz, const int32_t *tmesh, const int32_t *out_idx,
-                       double *phi, double *grad, int grad_stride, double *pairs);
+                       double *phi, double *grad, int grad_stride, double *pairs, void *part);
 
 // Newton (lss_kernels.hip)
 void launch_chart_init(Ctx &c, const double *chart_uv, int32_t np, int64_t N);
@@ -427,6 +431,7 @@ struct EvalBufs {
     int32_t *tstart, *tleaf, *ntiles, *order;
     void *sort_tmp;
     size_t sort_bytes;
+    void *part;                           // direct_part_bytes of the call, or null
     double *pairs;                        // statistics counters, or null
     const int32_t *n_dev;                 // target count on the device, or null
 };

@@ -126,7 +126,7 @@ void eval_noalloc(Ctx &c, const double *x, const int32_t *xm, int64_t n, double 
     std::string err;
     unsigned char *base = static_cast<unsigned char *>(noalloc_scratch(c.device, &err));
     if (!base) throw Error{LSS_EHIP, "lss_eval_noalloc: " + err};
-    const Layout L = layout_for(LSS_NOALLOC_MAX_TARGETS);
+    const Layout L = layout_for(n);
     if (L.total > kScratchBytes)
         throw Error{LSS_EHIP, "lss_eval_noalloc: scratch layout (" + std::to_string(L.total) +
                                   " bytes) exceeds the static array"};
@@ -162,6 +162,13 @@ void eval_noalloc(Ctx &c, const double *x, const int32_t *xm, int64_t n, double 
     b.order = reinterpret_cast<int32_t *>(base + L.order);
     b.sort_tmp = base + L.sort;
     b.sort_bytes = L.sort_bytes;
+    b.part = nullptr;
+    if (c.opt.far_field == LSS_FAR_DIRECT && direct_splits(c, n) > 1) {
+        // the partial sums of a split direct sum lie behind the buffers of n targets
+        if (L.total + direct_part_bytes(c, n) > kScratchBytes)
+            throw Error{LSS_EHIP, "lss_eval_noalloc: partial sums exceed the static array"};
+        b.part = base + L.total;
+    }
     b.pairs = nullptr;                  // no statistics: lss_get_stats keeps the last lss_eval's
     b.n_dev = words;
     if (c.opt.far_field == LSS_FAR_FMM) {

@@ -1,0 +1,59 @@
+"""The splits of the evaluation kernels at the sizes where a wrong range would
+show: one target, partly filled waves and tiles, node counts that leave a
+remainder of a chunk, ragged batches, and the counts on both sides of the rule
+that chooses a split."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1909_13356_amd as lss
+from workloads import dunavant6, cube_mesh, star_surface, triangle_diameters, bbox_targets, configs
+
+pytestmark = pytest.mark.gpu
+
+
+def _err(a, b):
+    return np.abs(a - b).max() / np.abs(b).max()
+
+
+# bars of the two precisions against the oracle (relative to the largest value)
+BAR = {lss.FP64: 1e-12, lss.MIXED: 1e-6}
+
+
+@pytest.mark.parametrize("prec", [lss.FP64, lss.MIXED])
+@pytest.mark.parametrize("n", [1, 64, 257, 4099])
+def test_direct_split_against_oracle(n, prec):
+    v, t = cube_mesh(9)                              # 972 triangles, 11 664 nodes: 45.6 chunks of 256
+    x = bbox_targets(v, n, pad=0.5, seed=n)
+    rule = dunavant6()
+    c = lss.Context()
+    c.set_options(precision=prec)
+    c.set_sources(v, t, rule)
+    c.set_sigma(0.1)
+    phi, grad = c.eval(x)
+    k = np.linspace(0, n - 1, min(n, 200)).astype(int)
+    # relative to the sum of the terms' magnitudes: one far target's Phi is all cancellation
+    op, og, ap, ag = oracle.evaluate(v, t, np.full(len(t), 0.1), rule, x[k], with_abs=True)
+    assert (np.abs(phi[k] - op) <= BAR[prec] * ap).all() and (np.abs(grad[k] - og).max(1) <= BAR[prec] * ag).all()
+    assert c.stats()["last_pairs"] == n * 12 * len(t)
+    phi2, _ = c.eval(x, want_grad=False)
+    assert np.array_equal(phi, phi2)
+
+
+@pytest.mark.parametrize("prec", [lss.FP64, lss.MIXED])
+def test_direct_split_matches_unsplit(prec):
+    """The same targets among 170 000 (one workgroup per tile: no split) and alone; a tile's origin and a partial
+    sum's chunk move, so the results agree to the rounding of the sums (1e-13 FP64, 1e-6 mixed: the bar)."""
+    parts = [star_surface(5, seed=1), star_surface(3, seed=2)]
+    meshes = [dict(verts=v, tris=t, sigma=0.5 * triangle_diameters(v, t),
+                   targets=bbox_targets(v, m, seed=7 + m)) for (v, t), m in zip(parts, (169_000, 1_000))]
+    b = configs.concat_batch(meshes)
+    c = lss.Context()
+    c.set_options(precision=prec)
+    c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+    c.set_sigma(b["sigma"])
+    p0, g0 = c.eval(b["targets"], x_mesh=b["target_mesh"])
+    k = np.concatenate([np.arange(0, 169_000, 400), np.arange(169_000, 170_000, 3)])
+    p1, g1 = c.eval(b["targets"][k], x_mesh=b["target_mesh"][k])
+    tol = {lss.FP64: 1e-13, lss.MIXED: 1e-6}[prec]
+    assert _err(p1, p0[k]) <= tol and _err(g1, g0[k]) <= tol
