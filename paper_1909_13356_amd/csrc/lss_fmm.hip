@@ -3,15 +3,26 @@
 // translation operators as dense real matrices, dipole P2M at the leaves, and
 // every translation (M2M, M2L, L2L) as a gathered matrix product
 //     Y[dst_j] += scale_j * Op * X[src_j]
-// on the FP64 matrix cores (v_mfma_f64_16x16x4f64).  M2L runs one launch per
-// displacement class (one dense operator per class, all levels share it in
-// box-scaled form); inside a launch every destination box appears once, so
-// the accumulation is race free and deterministic.
+// on the FP64 matrix cores (v_mfma_f64_16x16x4f64).  M2M and L2L run one
+// launch per level.  M2L has two forms, both race free and deterministic:
+//   FP64 contexts (m2l_plan, m2l_pass): all pairs sorted by operator, rotated
+//     so that the operators split in two halves; one product launch and one
+//     sum launch per block of target boxes, each pair's product in a slot of
+//     its own and the sums in a fixed order.
+//   mixed contexts: one launch per displacement class (one dense operator per
+//     class); inside a launch every destination box appears once.  The
+//     rotated form would change the far field by 1e-16, and a Newton iterate
+//     moved by that makes a few FP32 pair sums of a million nodes round the
+//     other way (up to 7e-9 sigma in a node's h); the mixed projection is
+//     kept the same bit for bit.  What it would gain there is small: 1 to 3 ms
+//     of a 52 ms batch, nothing at 2e6 triangles.
 #include <cstring>
 #include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <map>
+#include <vector>
 
 #include "fmm_math.h"
 #include "lss_internal.h"
@@ -58,6 +69,48 @@ __global__ void k_fill_op(int kind, int p, int ncp, int nops, const cd *__restri
         else v = fmm::folded_entry(fmm::L2LMap{tab}, kk, l, oi, n, m, ii);
     }
     ops[(int64_t)o * per + e] = v;
+}
+
+// Irregular tables (order 2p) of the M2L operators: thread (operator, m) runs
+// column m of fmm::irregular_table, the same recurrences
+__global__ void k_m2l_tables(int nops, const double *__restrict__ vecs, int order, int stride, cd *tabs) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int o = i / (order + 1), m = i % (order + 1);
+    if (o >= nops) return;
+    const double x = vecs[3 * o], y = vecs[3 * o + 1], z = vecs[3 * o + 2];
+    cd *T = tabs + (int64_t)o * stride;
+    const double r2 = x * x + y * y + z * z, ir2 = 1.0 / r2;
+    cd tm1 = {sqrt(ir2), 0.0}, tm2 = {0.0, 0.0};
+    for (int k = 1; k <= m; ++k) tm1 = fmm::cscale(fmm::cmul(tm1, cd{x, y}), -(2.0 * k - 1.0) * ir2);
+    T[fmm::tri(m, m)] = tm1;
+    for (int n = m + 1; n <= order; ++n) {
+        const double a = (2 * n - 1) * z, b = (double)(n - 1 + m) * (double)(n - 1 - m);
+        const cd tn = {(a * tm1.re - b * tm2.re) * ir2, (a * tm1.im - b * tm2.im) * ir2};
+        T[fmm::tri(n, m)] = tn;
+        tm2 = tm1;
+        tm1 = tn;
+    }
+}
+
+// M2L operator o of a displacement with y = 0 as its two halves: entry (row,
+// col) of the product of the Re parts at ops[2 o], of the Im parts at
+// ops[2 o + 1], k-major (col * ldr + row), rows and columns q = (n, m >= 0) in
+// the order of fmm::tri, zero beyond order p
+__global__ void k_fill_m2l(int p, int ldk, int ldr, int nops, const cd *__restrict__ tabs, int stride,
+                           const int32_t *__restrict__ qtab, double *ops) {
+    const int64_t per = (int64_t)ldk * ldr;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int o = blockIdx.y >> 1, im = blockIdx.y & 1;
+    if (e >= per || o >= nops) return;
+    const int col = (int)(e / ldr), row = (int)(e % ldr), nq = (p + 1) * (p + 2) / 2;
+    double v = 0.0;
+    if (row < nq && col < nq) {
+        const int tr = qtab[row], tc = qtab[col];
+        const int k = tr >> 24, l = (tr >> 16) & 0xff, n = tc >> 24, m = (tc >> 16) & 0xff;
+        if (!im || (l > 0 && m > 0))
+            v = fmm::folded_entry(fmm::M2LMap{tabs + (int64_t)o * stride}, k, l, im, n, m, im);
+    }
+    ops[(2 * (int64_t)o + im) * per + e] = v;
 }
 
 // ------------------------------------------------------------------ P2M
@@ -556,6 +609,275 @@ __global__ void k_small_pairs(const int64_t *__restrict__ beg, const int64_t *__
     }
 }
 
+// ------------------------------------------------------------------- M2L
+// A translation over v = (x, y, z) is a rotation about z by the angle of
+// (x, y), the translation over (rho, 0, |z|), rho = |(x, y)|, and the rotation
+// back; a negative z adds the signs (-1)^(n+m) on both sides:
+//     L_k^l = e^{-i l phi} s_kl sum_{n,m} A(k,l,n,m) s_nm e^{i m phi} M_n^m.
+// With y = 0 the operator A is real, so it acts on the Re and on the Im parts
+// apart: two products of half the rows and columns, i.e. half the operations
+// of the full matrix, and one operator serves every class of equal x^2 + y^2
+// and |z| (a "group": up to 16 classes, 60 to 70 groups where there were 850
+// classes at order 26).  The rotations are applied where the columns are
+// staged and where the products are stored.
+//
+// Pairs are sorted by (block of target boxes, group, class, box).  k_m2l takes
+// 64 pairs of one group x 64 rows (both halves) per workgroup and leaves each
+// pair's product in its own slot of Y; k_m2l_sum adds the products of a box in
+// rank order.  One launch of each per block, where one launch per class left
+// the chip idle between (and inside) thousands of short launches: 850 of them
+// took 14 ms of two streams for the 17 428 pairs of a 1728-triangle skeleton,
+// which are 0.3 ms of work.
+struct M2LArgs {
+    const uint64_t *key;        // sorted: (block << (kRankBits + shift)) | (rank << shift) | low bits of T
+    const int32_t *src;         // source box
+    const int32_t *ts;          // tile t holds the pairs ts[t] .. ts[t + 1) (at most kPairs, one group)
+    int tile0, ntiles;          // tiles of the block
+    int64_t p0;                 // first pair of the block
+    int shift, rowtiles;
+    const int32_t *info;        // per rank: group | angle << 10 | reflected << 18
+    const int32_t *grp;         // per group: slot, rows (q) and coefficients (real layout) of its order
+    const double *ops;          // slot: Re and Im halves, each ldk x ldr, k-major
+    int ldk, ldr;
+    const double2 *trig;        // (cos, sin) of m times the angle, m = 0 .. p, per angle
+    int p1;                     // p + 1
+    const int32_t *qtab;        // q -> index of Im (Re at m = 0) | m << 16 | n << 24; 0xffff past the order
+    const double *M;
+    int ncp;
+    double2 *Y;                 // products, ystride (Re, Im) pairs per pair of boxes
+    int ystride;
+};
+
+constexpr int kRankBits = 12;
+constexpr int kPairs = 64;      // pairs per tile
+constexpr int kQ = 64;          // rows (both halves) per workgroup
+constexpr int kKQ = 8;          // columns per staged block
+constexpr int kLd = kQ + 1;     // LDS row length
+static_assert(kNClass <= (1 << kRankBits), "the rank takes kRankBits bits of the key");
+
+__device__ __forceinline__ int rank_of(uint64_t key, int shift) { return (int)(key >> shift) & ((1 << kRankBits) - 1); }
+
+// Bound by the FP64 matrix cores.  64 rows x 64 pairs of both halves: wave w
+// owns 16 pairs and NS + NS accumulator tiles of 16 x 16 (NS = 4 but for the
+// last rows of a group).  The next block of kKQ columns is loaded into
+// registers while the MFMAs of the current one run.
+template <int NS>
+__device__ __forceinline__ void m2l_tile(const M2LArgs &a, int i0, int i1, int r0, int nq, int nkv, int slot,
+                                         double (&AR)[kKQ][kLd], double (&AI)[kKQ][kLd],
+                                         double (&BR)[kKQ][kLd], double (&BI)[kKQ][kLd]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t per_op = (int64_t)a.ldk * a.ldr;
+    // staging of the operator: column ak, ak + 4, rows ar
+    const int ak = threadIdx.x / kQ, ar = threadIdx.x % kQ;
+    const double *__restrict__ opr = a.ops + 2 * (int64_t)slot * per_op + (int64_t)ak * a.ldr + r0 + ar;
+    const double *__restrict__ opi = opr + per_op;
+    // staging of the columns: pair bc, rows bq, bq + 1 of the block
+    const int bc = threadIdx.x >> 2, bq = (threadIdx.x & 3) * 2;
+    const bool live = i0 + bc < i1;
+    const int jb = live ? i0 + bc : i0;
+    const int binfo = a.info[rank_of(a.key[jb], a.shift)];
+    const double *__restrict__ x = a.M + (int64_t)a.src[jb] * a.ncp;
+    const double2 *__restrict__ bt = a.trig + (int64_t)((binfo >> 10) & 255) * a.p1;
+    const int bflip = binfo >> 18;
+    double va[4], vb[4];
+    int fn[2], fm[2];                                      // (n, m) of the q that is fetched next
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        fn[i] = 0;
+        fm[i] = bq + i;
+        while (fm[i] > fn[i]) fm[i] -= ++fn[i];
+    }
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            va[2 * i] = opr[(int64_t)(k0 + 4 * i) * a.ldr];
+            va[2 * i + 1] = opi[(int64_t)(k0 + 4 * i) * a.ldr];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int n = fn[i], m = fm[i], off = fmm::iim(n, m), ore = m ? off - 1 : off;
+            // the order's leading nkv coefficients
+            const double vr = live && ore < nkv ? x[ore] : 0.0, vi = live && m && off < nkv ? x[off] : 0.0;
+            double2 cs = bt[m < a.p1 ? m : 0];
+            if (bflip & (n + m)) cs = double2{-cs.x, -cs.y};
+            fm[i] += kKQ;
+            while (fm[i] > fn[i]) fm[i] -= ++fn[i];
+            vb[2 * i] = cs.x * vr - cs.y * vi;
+            vb[2 * i + 1] = cs.y * vr + cs.x * vi;
+        }
+    };
+    d4 cr[NS], ci[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) cr[i] = ci[i] = d4{0.0, 0.0, 0.0, 0.0};
+    fetch(0);
+    for (int k0 = 0; k0 < nq; k0 += kKQ) {
+        __syncthreads();                                   // previous block's MFMAs are done with LDS
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            AR[ak + 4 * i][ar] = va[2 * i];
+            AI[ak + 4 * i][ar] = va[2 * i + 1];
+            BR[bq + i][bc] = vb[2 * i];
+            BI[bq + i][bc] = vb[2 * i + 1];
+        }
+        __syncthreads();
+        if (k0 + kKQ < nq) fetch(k0 + kKQ);
+#pragma unroll
+        for (int kk = 0; kk < kKQ; kk += 4) {
+            const double vr = BR[kk + (lane >> 4)][16 * w + (lane & 15)], vi = BI[kk + (lane >> 4)][16 * w + (lane & 15)];
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                cr[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(AR[kk + (lane >> 4)][16 * i + (lane & 15)], vr, cr[i], 0, 0, 0);
+                ci[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(AI[kk + (lane >> 4)][16 * i + (lane & 15)], vi, ci[i], 0, 0, 0);
+            }
+        }
+    }
+    const int j = i0 + 16 * w + (lane & 15);
+    if (j >= i1) return;
+    const int info = a.info[rank_of(a.key[j], a.shift)];
+    const double2 *__restrict__ tr = a.trig + (int64_t)((info >> 10) & 255) * a.p1;
+    const int flip = info >> 18;
+    double2 *__restrict__ y = a.Y + (j - a.p0) * a.ystride;
+    // v_mfma_f64_16x16x4f64 accumulator: register q of lane l holds row (l/16) + 4q, column l%16
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = r0 + 16 * i + (lane >> 4) + 4 * q;
+            if (row >= nq) continue;
+            const int t = a.qtab[row], off = t & 0xffff, m = (t >> 16) & 0xff;
+            double2 cs = tr[m];
+            if (flip & ((t >> 24) + m)) cs = double2{-cs.x, -cs.y};
+            const double re = cs.x * cr[i][q] + cs.y * ci[i][q], im = cs.x * ci[i][q] - cs.y * cr[i][q];
+            y[row] = double2{(m ? off - 1 : off) < nkv ? re : 0.0, off < nkv ? im : 0.0};
+        }
+}
+
+// Workgroups go to the 8 XCDs in turn; the work is dealt in runs of kXcdTiles
+// tiles per XCD, so that the row tiles of one tile and its neighbours (same
+// operator) share an L2.  Longer runs would leave XCDs idle: the far groups
+// have a fifth of the near groups' work (2e5 graded triangles, order 26: 24 ms
+// with one run per XCD, 14.6 ms with these).
+constexpr int kXcdTiles = 8;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_m2l(M2LArgs a) {
+    __shared__ double AR[kKQ][kLd], AI[kKQ][kLd], BR[kKQ][kLd], BI[kKQ][kLd];
+    const int run = kXcdTiles * a.rowtiles, i = (int)(blockIdx.x >> 3);
+    const int rt = i % run, tl = (i / run * 8 + (int)(blockIdx.x & 7)) * kXcdTiles + rt / a.rowtiles;
+    if (tl >= a.ntiles) return;
+    const int tile = a.tile0 + tl, r0 = (rt % a.rowtiles) * kQ;
+    const int i0 = a.ts[tile], i1 = a.ts[tile + 1];
+    const int grp = a.info[rank_of(a.key[i0], a.shift)] & 1023;
+    const int slot = a.grp[3 * grp], nq = a.grp[3 * grp + 1], nkv = a.grp[3 * grp + 2];
+    if (r0 >= nq) return;
+    switch ((nq - r0 + 15) / 16) {                         // uniform
+        case 1: m2l_tile<1>(a, i0, i1, r0, nq, nkv, slot, AR, AI, BR, BI); break;
+        case 2: m2l_tile<2>(a, i0, i1, r0, nq, nkv, slot, AR, AI, BR, BI); break;
+        case 3: m2l_tile<3>(a, i0, i1, r0, nq, nkv, slot, AR, AI, BR, BI); break;
+        default: m2l_tile<4>(a, i0, i1, r0, nq, nkv, slot, AR, AI, BR, BI); break;
+    }
+}
+
+// Local expansion of box b0 + blockIdx.x: its pairs' products added in rank
+// order, times 1 / side; boxes without pairs and the padding get zeros.
+// Bound by reading Y (16 bytes per row and pair, coalesced).
+__global__ __launch_bounds__(256) void k_m2l_sum(M2LArgs a, int64_t b0, const int32_t *__restrict__ beg,
+                                                 const int32_t *__restrict__ end, const int32_t *__restrict__ list,
+                                                 int nqmax, Geo g, const int32_t *__restrict__ lev, double *L) {
+    __shared__ int spair[256], snq[256];
+    const int64_t T = b0 + blockIdx.x;
+    const int e0 = beg[T], e1 = end[T], tid = threadIdx.x;
+    const double sc = 1.0 / box_side(g.root, g.bmesh, (int32_t)T, lev[T]);
+    double *__restrict__ l = L + T * a.ncp;
+    for (int q0 = 0; q0 < nqmax; q0 += 256) {
+        const int q = q0 + tid;
+        double re = 0.0, im = 0.0;
+        for (int e = e0; e < e1; e += 256) {
+            const int n = min(256, e1 - e);
+            __syncthreads();
+            if (tid < n) {
+                const int j = list[e + tid];
+                spair[tid] = (int)(j - a.p0);
+                snq[tid] = a.grp[3 * (a.info[rank_of(a.key[j], a.shift)] & 1023) + 1];
+            }
+            __syncthreads();
+#pragma unroll 4
+            for (int k = 0; k < n; ++k)
+                if (q < snq[k]) {
+                    const double2 v = a.Y[(int64_t)spair[k] * a.ystride + q];
+                    re += v.x;
+                    im += v.y;
+                }
+        }
+        if (q < nqmax) {
+            const int t = a.qtab[q], off = t & 0xffff, m = (t >> 16) & 0xff;
+            l[m ? off - 1 : off] = sc * re;
+            if (m) l[off] = sc * im;
+        }
+    }
+    const int nc = a.p1 * a.p1;
+    if (nc + tid < a.ncp) l[nc + tid] = 0.0;               // ncp - nc < 16
+}
+
+// plan: keys by (block, rank, box) from the emitted (class << 32 | T); word 0: the count
+__global__ void k_m2l_rekey(int64_t n, const int32_t *__restrict__ rank, int shift, uint64_t *key, int32_t *word) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *word = (int32_t)n;
+    if (i >= n) return;
+    const uint32_t cls = (uint32_t)(key[i] >> 32), T = (uint32_t)key[i];
+    key[i] = ((uint64_t)(T >> shift) << (kRankBits + shift)) | ((uint64_t)rank[cls] << shift) |
+             (T & ((1u << shift) - 1u));
+}
+
+// Sorted pairs: tile heads (every kPairs-th pair of a (block, group) segment,
+// the segment starting at the first key with its block and its group's lowest
+// rank), the groups in use, the first pair of every block, and the pairs
+// keyed by target box for the sums
+__global__ void k_m2l_mark(int64_t n, const uint64_t *__restrict__ key, int shift, int nblk,
+                           const int32_t *__restrict__ info, const int32_t *__restrict__ grp_rank, int32_t *flag,
+                           int32_t *pos, int32_t *used, int32_t *blk, uint64_t *tkey, int32_t *tval) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const uint64_t k = key[i];
+    const int64_t b = (int64_t)(k >> (kRankBits + shift)), bp = i > 0 ? (int64_t)(key[i - 1] >> (kRankBits + shift)) : -1;
+    for (int64_t q = bp + 1; q <= b; ++q) blk[q] = (int32_t)i;
+    if (i == n - 1)
+        for (int64_t q = b + 1; q <= nblk; ++q) blk[q] = (int32_t)n;
+    const int g = info[rank_of(k, shift)] & 1023;
+    const uint64_t first = ((uint64_t)b << (kRankBits + shift)) | ((uint64_t)grp_rank[g] << shift);
+    int64_t lo = 0, hi = i;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (key[mid] < first) lo = mid + 1; else hi = mid;
+    }
+    if (lo == i) used[g] = 1;
+    flag[i] = (i - lo) % kPairs == 0 ? 1 : 0;
+    pos[i] = (int32_t)i;
+    tkey[i] = ((uint64_t)b << shift) | (k & ((1ull << shift) - 1ull));
+    tval[i] = (int32_t)i;
+}
+
+// first tile of every block, and the end of the tile list
+__global__ void k_m2l_blk_tiles(int nblk, const int32_t *__restrict__ blk, const int32_t *__restrict__ ntiles,
+                                int32_t n, int32_t *ts, int32_t *blk_tile) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b > nblk) return;
+    const int nt = *ntiles;
+    if (b == 0) ts[nt] = n;
+    int lo = 0, hi = nt;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ts[mid] < blk[b]) lo = mid + 1; else hi = mid;
+    }
+    blk_tile[b] = lo;
+}
+
+__global__ void k_m2l_ranges(int64_t n, const uint64_t *__restrict__ key, int32_t *beg, int32_t *end) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const uint64_t T = key[i];
+    if (i == 0 || key[i - 1] != T) beg[T] = (int32_t)i;
+    if (i == n - 1 || key[i + 1] != T) end[T] = (int32_t)(i + 1);
+}
+
 // class index -> offset vector
 void class_vec(int cls, double v[3]) {
     const int W = 2 * kR + 1;
@@ -599,6 +921,249 @@ void build_ops(Ctx &c, int kind, int nops, const std::vector<double> &vecs, int 
     LSS_HIP(hipStreamSynchronize(c.stream));
 }
 
+// The displacement classes ordered by group (equal x^2 + y^2 and |z|): rank of
+// each class, and per rank its group, angle index and reflection.
+struct M2LClasses {
+    int ngroups = 0;
+    std::vector<int32_t> rank, info, grp_rank;     // per class; per rank; lowest rank of each group
+    std::vector<double> vec;                       // per group: (rho, 0, |z|)
+    M2LClasses() {
+        const int W = 2 * kR + 1;
+        std::map<std::pair<int, int>, std::vector<int>> by;
+        for (int cls = 0; cls < kNClass; ++cls) {
+            double v[3];
+            class_vec(cls, v);
+            by[{(int)(v[0] * v[0] + v[1] * v[1]), (int)std::fabs(v[2])}].push_back(cls);
+        }
+        ngroups = (int)by.size();
+        rank.assign(kNClass, 0);
+        info.assign(kNClass, 0);
+        int r = 0, g = 0;
+        for (const auto &e : by) {
+            grp_rank.push_back(r);
+            vec.insert(vec.end(), {std::sqrt((double)e.first.first), 0.0, (double)e.first.second});
+            for (int cls : e.second) {
+                double v[3];
+                class_vec(cls, v);
+                rank[cls] = r;
+                info[r] = g | (((int)v[0] + kR) * W + (int)v[1] + kR) << 10 | (v[2] < 0.0 ? 1 << 18 : 0);
+                ++r;
+            }
+            ++g;
+        }
+    }
+};
+const M2LClasses &m2l_classes() {
+    static const M2LClasses k;
+    return k;
+}
+static_assert((2 * kR + 1) * (2 * kR + 1) <= 256, "the angle index takes 8 bits of a rank's info");
+
+// The M2L plan of the emitted list: pairs sorted by (block, rank, box), tiles,
+// and each box's pairs.  A block holds 2^shift target boxes, as many as keep
+// the products of an average block near kM2LBytes: large enough to fill the
+// chip several times over (about 1e5 pairs), small enough that the expansions
+// of a block's sources stay in the caches between its groups.
+constexpr double kM2LBytes = 1024.0 * 1024.0 * 1024.0;
+
+void m2l_plan(Ctx &c) {
+    Tree &t = c.tree;
+    const int64_t n = t.n_m2l;
+    if (n == 0) return;
+    const M2LClasses &cl = m2l_classes();
+    const int p = t.p;
+    const double per_box = (double)n / (double)t.nboxes * 8.0 * (p + 1) * (p + 2);
+    int shift = 0;
+    while ((int64_t(1) << shift) < t.nboxes && 2.0 * per_box * (double)(int64_t(1) << shift) <= kM2LBytes) ++shift;
+    t.m2l_shift = shift;
+    const int nblk = (int)((t.nboxes - 1) >> shift) + 1;
+    if (!t.m2l_tab.p) {
+        t.m2l_tab.ensure(4 * (2 * kNClass + cl.ngroups));
+        LSS_HIP(hipMemcpyAsync(t.m2l_tab.p, cl.rank.data(), 4 * kNClass, hipMemcpyHostToDevice, c.stream));
+        LSS_HIP(hipMemcpyAsync(t.m2l_tab.as<int32_t>() + kNClass, cl.info.data(), 4 * kNClass, hipMemcpyHostToDevice,
+                               c.stream));
+        LSS_HIP(hipMemcpyAsync(t.m2l_tab.as<int32_t>() + 2 * kNClass, cl.grp_rank.data(), 4 * cl.ngroups,
+                               hipMemcpyHostToDevice, c.stream));
+    }
+    const int32_t *rank = t.m2l_tab.as<int32_t>(), *info = rank + kNClass, *grp_rank = info + kNClass;
+    // meta: used flag per group, first pair per block (+ end), first tile per block (+ end), count, tiles
+    const int64_t nmeta = cl.ngroups + 2 * (nblk + 1) + 2;
+    t.m2l_meta.ensure(4 * nmeta);
+    int32_t *used = t.m2l_meta.as<int32_t>(), *blk = used + cl.ngroups, *blk_tile = blk + nblk + 1,
+            *count = blk_tile + nblk + 1, *ntiles = count + 1;
+    LSS_HIP(hipMemsetAsync(used, 0, 4 * cl.ngroups, c.stream));
+    hipLaunchKernelGGL(k_m2l_rekey, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, rank, shift,
+                       t.m2l_key.as<uint64_t>(), count);
+    t.m2l_key2.ensure(8 * n);
+    t.m2l_val2.ensure(4 * n);
+    int bb = 1;
+    while ((int64_t(1) << bb) < nblk) ++bb;
+    // own sort workspace (the near lists are sorted on the other stream meanwhile)
+    const size_t stb = sort_pairs_u64_tmp_bytes(n);
+    t.m2l_tmp.ensure(stb);
+    sort_pairs_u64(t.m2l_tmp.p, stb, t.m2l_key.as<uint64_t>(), t.m2l_key2.as<uint64_t>(), t.m2l_val.as<int32_t>(),
+                   t.m2l_val2.as<int32_t>(), n, 0, kRankBits + shift + bb, c.stream);
+    t.m2l_flag.ensure(4 * n);
+    t.m2l_pos.ensure(4 * n);
+    t.m2l_ts.ensure(4 * (n + 1));
+    t.m2l_csr_key.ensure(8 * n);
+    t.m2l_csr_key2.ensure(8 * n);
+    t.m2l_csr.ensure(4 * n);
+    t.m2l_csr2.ensure(4 * n);
+    hipLaunchKernelGGL(k_m2l_mark, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, t.m2l_key2.as<uint64_t>(), shift,
+                       nblk, info, grp_rank, t.m2l_flag.as<int32_t>(), t.m2l_pos.as<int32_t>(), used, blk,
+                       t.m2l_csr_key.as<uint64_t>(), t.m2l_csr.as<int32_t>());
+    LSS_CHECK_LAUNCH("k_m2l_mark");
+    t.m2l_bsum.ensure(4 * ((size_t)compact_blocks(n) + 2));
+    compact_flags(c, n, count, t.m2l_flag.as<int32_t>(), t.m2l_pos.as<int32_t>(), t.m2l_ts.as<int32_t>(), ntiles,
+                  t.m2l_bsum.as<int32_t>());
+    hipLaunchKernelGGL(k_m2l_blk_tiles, dim3(grid_for(nblk + 1)), dim3(kBlk), 0, c.stream, nblk, blk, ntiles,
+                       (int32_t)n, t.m2l_ts.as<int32_t>(), blk_tile);
+    LSS_CHECK_LAUNCH("k_m2l_blk_tiles");
+    std::vector<int32_t> h(cl.ngroups + 2 * (nblk + 1));
+    LSS_HIP(hipMemcpyAsync(h.data(), used, 4 * h.size(), hipMemcpyDeviceToHost, c.stream));
+    // the pairs of every box, in rank order (the sort is stable)
+    int tb = 1;
+    while ((int64_t(1) << tb) < t.nboxes) ++tb;
+    sort_pairs_u64(t.m2l_tmp.p, stb, t.m2l_csr_key.as<uint64_t>(), t.m2l_csr_key2.as<uint64_t>(),
+                   t.m2l_csr.as<int32_t>(), t.m2l_csr2.as<int32_t>(), n, 0, tb, c.stream);
+    t.m2l_beg.ensure(4 * t.nboxes);
+    t.m2l_end.ensure(4 * t.nboxes);
+    LSS_HIP(hipMemsetAsync(t.m2l_beg.p, 0, 4 * t.nboxes, c.stream));
+    LSS_HIP(hipMemsetAsync(t.m2l_end.p, 0, 4 * t.nboxes, c.stream));
+    hipLaunchKernelGGL(k_m2l_ranges, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, t.m2l_csr_key2.as<uint64_t>(),
+                       t.m2l_beg.as<int32_t>(), t.m2l_end.as<int32_t>());
+    LSS_CHECK_LAUNCH("k_m2l_ranges");
+    LSS_HIP(hipStreamSynchronize(c.stream));
+    t.m2l_used.clear();
+    for (int g = 0; g < cl.ngroups; ++g)
+        if (h[g]) t.m2l_used.push_back(g);
+    t.m2l_blk.assign(h.begin() + cl.ngroups, h.begin() + cl.ngroups + nblk + 1);
+    t.m2l_blk_tile.assign(h.begin() + cl.ngroups + nblk + 1, h.end());
+}
+
+// M2L of every pair: t.L from t.M (written whole), operators of the groups in
+// use built first where they are missing.  Each group runs at the order that
+// its distance needs (m2l_order): the leading rows and columns of its operator.
+void m2l_pass(Ctx &c, int p, int ncp) {
+    Tree &t = c.tree;
+    if (t.n_m2l == 0) {
+        launch_fill_zero(c, t.L.as<double>(), t.nboxes * (int64_t)ncp);
+        return;
+    }
+    const M2LClasses &cl = m2l_classes();
+    const int nqmax = (p + 1) * (p + 2) / 2;
+    const int ldk = (int)ceil_div(nqmax, kKQ) * kKQ, ldr = (int)ceil_div(nqmax, kQ) * kQ;
+    const int64_t per = 2 * (int64_t)ldk * ldr;            // both halves
+    if (t.m2l_p != p) {     // index table, rotations by every angle: ((x + i y) / rho)^m in extended precision
+        std::vector<int32_t> qtab(ldk, 0xffff);            // padding: past every order
+        for (int n = 0; n <= p; ++n)
+            for (int m = 0; m <= n; ++m)
+                qtab[fmm::tri(n, m)] = (m ? fmm::iim(n, m) : fmm::ire(n, 0)) | m << 16 | n << 24;
+        const int W = 2 * kR + 1;
+        std::vector<double> trig((size_t)2 * W * W * (p + 1));
+        for (int k = 0; k < W * W; ++k) {
+            const long double x = k / W - kR, y = k % W - kR, rho = std::sqrt(x * x + y * y);
+            const long double cx = rho > 0 ? x / rho : 1.0L, sx = rho > 0 ? y / rho : 0.0L;
+            long double cm = 1.0L, sm = 0.0L;
+            for (int m = 0; m <= p; ++m) {
+                trig[2 * ((size_t)k * (p + 1) + m)] = (double)cm;
+                trig[2 * ((size_t)k * (p + 1) + m) + 1] = (double)sm;
+                const long double q = cm * cx - sm * sx;
+                sm = sm * cx + cm * sx;
+                cm = q;
+            }
+        }
+        t.m2l_qtab.ensure(4 * qtab.size());
+        t.m2l_trig.ensure(8 * trig.size());
+        LSS_HIP(hipMemcpyAsync(t.m2l_qtab.p, qtab.data(), 4 * qtab.size(), hipMemcpyHostToDevice, c.stream));
+        LSS_HIP(hipMemcpyAsync(t.m2l_trig.p, trig.data(), 8 * trig.size(), hipMemcpyHostToDevice, c.stream));
+        LSS_HIP(hipStreamSynchronize(c.stream));           // the host tables end here
+        t.op_group_slot.assign(cl.ngroups, -1);
+        t.m2l_p = p;
+    }
+    std::vector<int> need;
+    int have = 0;
+    for (int s : t.op_group_slot) have += s >= 0;
+    for (int g : t.m2l_used)
+        if (t.op_group_slot[g] < 0) need.push_back(g);
+    if (!need.empty()) {
+        t.opM2G.grow_copy(sizeof(double) * (size_t)(have + (int64_t)need.size()) * per,
+                          sizeof(double) * (size_t)have * per, c.stream);
+        const int nops = (int)need.size(), order = 2 * p, stride = fmm::tri(order, order) + 1;
+        std::vector<double> v;
+        for (int g : need) v.insert(v.end(), cl.vec.begin() + 3 * g, cl.vec.begin() + 3 * g + 3);
+        DBuf dv, tabs;
+        dv.ensure(8 * v.size());
+        tabs.ensure(sizeof(cd) * (size_t)stride * nops);
+        LSS_HIP(hipMemcpyAsync(dv.p, v.data(), 8 * v.size(), hipMemcpyHostToDevice, c.stream));
+        hipLaunchKernelGGL(k_m2l_tables, dim3(grid_for((int64_t)nops * (order + 1), 64)), dim3(64), 0, c.stream, nops,
+                           dv.as<double>(), order, stride, tabs.as<cd>());
+        hipLaunchKernelGGL(k_fill_m2l, dim3(grid_for((int64_t)ldk * ldr), 2 * nops), dim3(kBlk), 0, c.stream, p, ldk,
+                           ldr, nops, tabs.as<cd>(), stride, t.m2l_qtab.as<int32_t>(),
+                           t.opM2G.as<double>() + (int64_t)have * per);
+        LSS_CHECK_LAUNCH("k_fill_m2l");
+        LSS_HIP(hipStreamSynchronize(c.stream));
+        for (int g : need) t.op_group_slot[g] = have++;
+    }
+    // slot, rows and coefficients of every group in use (K may change between
+    // builds): the leading coefficients in and out, (p_v + 1)^2 rounded up to
+    // 16 in the real layout, and the q whose Re is among them
+    t.h_m2l_grp.assign(3 * cl.ngroups, 0);
+    int rowmax = 0;
+    for (int g : t.m2l_used) {
+        const int pv = m2l_order(p, t.K, &cl.vec[3 * g]);
+        const int nkv = std::min((p + 1) * (p + 1), (int)ceil_div((int64_t)(pv + 1) * (pv + 1), kKB) * kKB);
+        int nq = 0;
+        for (int n = 0; n <= p; ++n)
+            for (int m = 0; m <= n; ++m)
+                if (fmm::ire(n, m) < nkv) nq = fmm::tri(n, m) + 1;
+        t.h_m2l_grp[3 * g] = t.op_group_slot[g];
+        t.h_m2l_grp[3 * g + 1] = nq;
+        t.h_m2l_grp[3 * g + 2] = nkv;
+        rowmax = std::max(rowmax, nq);
+    }
+    t.m2l_grp.ensure(4 * t.h_m2l_grp.size());
+    LSS_HIP(hipMemcpyAsync(t.m2l_grp.p, t.h_m2l_grp.data(), 4 * t.h_m2l_grp.size(), hipMemcpyHostToDevice, c.stream));
+    const int nblk = (int)t.m2l_blk.size() - 1;
+    int64_t most = 0;
+    for (int b = 0; b < nblk; ++b) most = std::max(most, t.m2l_blk[b + 1] - t.m2l_blk[b]);
+    t.m2l_y.ensure(sizeof(double2) * (size_t)most * rowmax);
+    M2LArgs a;
+    a.key = t.m2l_key2.as<uint64_t>();
+    a.src = t.m2l_val2.as<int32_t>();
+    a.ts = t.m2l_ts.as<int32_t>();
+    a.shift = t.m2l_shift;
+    a.rowtiles = (int)ceil_div(rowmax, kQ);
+    a.info = t.m2l_tab.as<int32_t>() + kNClass;
+    a.grp = t.m2l_grp.as<int32_t>();
+    a.ops = t.opM2G.as<double>();
+    a.ldk = ldk;
+    a.ldr = ldr;
+    a.trig = t.m2l_trig.as<double2>();
+    a.p1 = p + 1;
+    a.qtab = t.m2l_qtab.as<int32_t>();
+    a.M = t.M.as<double>();
+    a.ncp = ncp;
+    a.Y = t.m2l_y.as<double2>();
+    a.ystride = rowmax;
+    const Geo g{t.root.as<double>(), t.bmesh.as<int32_t>()};
+    for (int b = 0; b < nblk; ++b) {
+        a.tile0 = t.m2l_blk_tile[b];
+        a.ntiles = t.m2l_blk_tile[b + 1] - a.tile0;
+        a.p0 = t.m2l_blk[b];
+        if (a.ntiles > 0) {
+            const int64_t wg = ceil_div(a.ntiles, 8 * kXcdTiles) * 8 * kXcdTiles * a.rowtiles;
+            hipLaunchKernelGGL(k_m2l, dim3((unsigned)wg), dim3(256), 0, c.stream, a);
+        }
+        const int64_t b0 = (int64_t)b << t.m2l_shift, nb = std::min<int64_t>(int64_t(1) << t.m2l_shift, t.nboxes - b0);
+        hipLaunchKernelGGL(k_m2l_sum, dim3((unsigned)nb), dim3(256), 0, c.stream, a, b0, t.m2l_beg.as<int32_t>(),
+                           t.m2l_end.as<int32_t>(), t.m2l_csr2.as<int32_t>(), nqmax, g, t.level.as<int32_t>(),
+                           t.L.as<double>());
+        LSS_CHECK_LAUNCH("k_m2l");
+    }
+}
+
 }  // namespace
 
 // Expansions at the leaves (P2M) and up the tree (M2M) on c.stream; the
@@ -607,7 +1172,8 @@ void upward_pass(Ctx &c, int p, int ncp, DBuf &flag, DBuf &ids, DBuf &leaves, DB
     Tree &t = c.tree;
     // expansions
     LSS_HIP(hipMemsetAsync(t.M.p, 0, sizeof(double) * t.nboxes * ncp, c.stream));
-    LSS_HIP(hipMemsetAsync(t.L.p, 0, sizeof(double) * t.nboxes * ncp, c.stream));
+    if (c.opt.precision == LSS_MIXED)                       // m2l_pass writes all of L
+        LSS_HIP(hipMemsetAsync(t.L.p, 0, sizeof(double) * t.nboxes * ncp, c.stream));
     Geo g{t.root.as<double>(), t.bmesh.as<int32_t>()};
     // P2M on the non-empty leaves
     flag.ensure(4 * t.nboxes); ids.ensure(4 * t.nboxes); leaves.ensure(4 * t.nboxes); nleaf.ensure(16);
@@ -645,67 +1211,15 @@ void upward_pass(Ctx &c, int p, int ncp, DBuf &flag, DBuf &ids, DBuf &leaves, DB
     }
 }
 
-void build_fmm(Ctx &c) {
-    build_tree_boxes(c);
+// M2L of a mixed context, class by class, into t.L (cleared by upward_pass)
+void m2l_classwise(Ctx &c, int p, int ncp) {
     Tree &t = c.tree;
-    const int p = fmm_order_for(c);
-    const int ncp = (int)ceil_div(fmm::ncoef(p), kKB) * kKB;
     const int64_t per = (int64_t)ncp * ncp;
-    // operators: M2M / L2L for the 8 octants, M2L for the classes in use
-    if (t.ops_p != p) {
-        std::vector<double> w(24);
-        for (int o = 0; o < 8; ++o) {
-            w[3 * o] = (o & 1) ? 0.5 : -0.5;
-            w[3 * o + 1] = ((o >> 1) & 1) ? 0.5 : -0.5;
-            w[3 * o + 2] = ((o >> 2) & 1) ? 0.5 : -0.5;
-        }
-        t.opM2M.ensure(sizeof(double) * 8 * per);
-        t.opL2L.ensure(sizeof(double) * 8 * per);
-        build_ops(c, 1, 8, w, p, ncp, t.opM2M.as<double>());
-        build_ops(c, 2, 8, w, p, ncp, t.opL2L.as<double>());
-        t.op_class_slot.assign(kNClass, -1);
-        t.opM2L.release();
-        t.ops_p = p;
-    }
-    t.p = p;
-    t.ncp = ncp;
-    t.M.ensure(sizeof(double) * t.nboxes * ncp);
-    t.L.ensure(sizeof(double) * t.nboxes * ncp);
-    // The upward pass (P2M, M2M) needs only the boxes: it runs on the
-    // auxiliary stream while the interaction lists are built on the context
-    // stream; the M2L waits for both.  The direct and M2P lists are sorted
-    // on the auxiliary stream after the upward pass, beside the
-    // translations; the context stream waits for them before returning.
-    // Same kernels, same order per buffer, so the results do not depend on
-    // the overlap.
-    if (!c.aux_stream) {
-        LSS_HIP(hipStreamCreateWithFlags(&c.aux_stream, hipStreamNonBlocking));
-        for (hipEvent_t &e : c.aux_ev) LSS_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    }
     struct StreamSwap {
         Ctx &c;
         hipStream_t saved;
         ~StreamSwap() { c.stream = saved; }
     };
-    LSS_HIP(hipEventRecord(c.aux_ev[0], c.stream));
-    LSS_HIP(hipStreamWaitEvent(c.aux_stream, c.aux_ev[0], 0));
-    DBuf flag, ids, leaves, nleaf;
-    {
-        StreamSwap swap{c, c.stream};
-        c.stream = c.aux_stream;
-        upward_pass(c, p, ncp, flag, ids, leaves, nleaf);
-        LSS_HIP(hipEventRecord(c.aux_ev[1], c.aux_stream));
-    }
-    build_tree_lists(c);
-    LSS_HIP(hipEventRecord(c.aux_ev[2], c.stream));        // lists emitted, M2L list sorted
-    {
-        StreamSwap swap{c, c.stream};
-        c.stream = c.aux_stream;
-        LSS_HIP(hipStreamWaitEvent(c.aux_stream, c.aux_ev[2], 0));
-        sort_near_lists(c);
-        LSS_HIP(hipEventRecord(c.aux_ev[3], c.aux_stream));
-    }
-    LSS_HIP(hipStreamWaitEvent(c.stream, c.aux_ev[1], 0));
     {   // M2L operators of the classes in use not built yet
         std::vector<int> need;
         for (int cls : t.class_used)
@@ -831,6 +1345,76 @@ void build_fmm(Ctx &c) {
         if (!on_aux[i]) m2l(jobs[i], t.L.as<double>());
     LSS_HIP(hipStreamWaitEvent(c.stream, c.aux_ev[5], 0));
     launch_add(c, t.L.as<double>(), t.L2.as<double>(), t.nboxes * (int64_t)ncp);
+}
+
+void build_fmm(Ctx &c) {
+    build_tree_boxes(c);
+    Tree &t = c.tree;
+    const int p = fmm_order_for(c);
+    const int ncp = (int)ceil_div(fmm::ncoef(p), kKB) * kKB;
+    const int64_t per = (int64_t)ncp * ncp;
+    // operators: M2M / L2L for the 8 octants, M2L for the classes in use
+    if (t.ops_p != p) {
+        std::vector<double> w(24);
+        for (int o = 0; o < 8; ++o) {
+            w[3 * o] = (o & 1) ? 0.5 : -0.5;
+            w[3 * o + 1] = ((o >> 1) & 1) ? 0.5 : -0.5;
+            w[3 * o + 2] = ((o >> 2) & 1) ? 0.5 : -0.5;
+        }
+        t.opM2M.ensure(sizeof(double) * 8 * per);
+        t.opL2L.ensure(sizeof(double) * 8 * per);
+        build_ops(c, 1, 8, w, p, ncp, t.opM2M.as<double>());
+        build_ops(c, 2, 8, w, p, ncp, t.opL2L.as<double>());
+        t.op_class_slot.assign(kNClass, -1);
+        t.opM2L.release();
+        t.ops_p = p;
+    }
+    t.p = p;
+    t.ncp = ncp;
+    t.M.ensure(sizeof(double) * t.nboxes * ncp);
+    t.L.ensure(sizeof(double) * t.nboxes * ncp);
+    // The upward pass (P2M, M2M) needs only the boxes: it runs on the
+    // auxiliary stream while the interaction lists are built on the context
+    // stream; the M2L waits for both.  The direct and M2P lists are sorted
+    // on the auxiliary stream after the upward pass, beside the
+    // translations; the context stream waits for them before returning.
+    // Same kernels, same order per buffer, so the results do not depend on
+    // the overlap.
+    if (!c.aux_stream) {
+        LSS_HIP(hipStreamCreateWithFlags(&c.aux_stream, hipStreamNonBlocking));
+        for (hipEvent_t &e : c.aux_ev) LSS_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    }
+    struct StreamSwap {
+        Ctx &c;
+        hipStream_t saved;
+        ~StreamSwap() { c.stream = saved; }
+    };
+    LSS_HIP(hipEventRecord(c.aux_ev[0], c.stream));
+    LSS_HIP(hipStreamWaitEvent(c.aux_stream, c.aux_ev[0], 0));
+    DBuf flag, ids, leaves, nleaf;
+    {
+        StreamSwap swap{c, c.stream};
+        c.stream = c.aux_stream;
+        upward_pass(c, p, ncp, flag, ids, leaves, nleaf);
+        LSS_HIP(hipEventRecord(c.aux_ev[1], c.aux_stream));
+    }
+    build_tree_lists(c);
+    LSS_HIP(hipEventRecord(c.aux_ev[2], c.stream));        // lists emitted, M2L list sorted
+    {
+        StreamSwap swap{c, c.stream};
+        c.stream = c.aux_stream;
+        LSS_HIP(hipStreamWaitEvent(c.aux_stream, c.aux_ev[2], 0));
+        sort_near_lists(c);
+        LSS_HIP(hipEventRecord(c.aux_ev[3], c.aux_stream));
+    }
+    if (c.opt.precision == LSS_MIXED) {
+        LSS_HIP(hipStreamWaitEvent(c.stream, c.aux_ev[1], 0));
+        m2l_classwise(c, p, ncp);
+    } else {
+        m2l_plan(c);
+        LSS_HIP(hipStreamWaitEvent(c.stream, c.aux_ev[1], 0));
+        m2l_pass(c, p, ncp);
+    }
     // downward pass: L2L from level 0 to depth-1 into their children
     for (int lvl = 1; lvl <= t.depth; ++lvl) {
         const int64_t base = t.level_begin[lvl], npar = (t.level_begin[lvl + 1] - base) / 8;

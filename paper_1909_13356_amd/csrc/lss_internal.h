@@ -212,10 +212,19 @@ struct Tree {
     int64_t n_m2p = 0;
     DBuf m2p_beg, m2p_end;                    // per box, int32 offsets into the sorted m2p list
     DBuf near_cnt;                            // per box + per mesh (outside targets): cost of a target in node pairs
-    DBuf m2l_key, m2l_key2, m2l_val, m2l_val2;    // u64 (class<<32|T), int32 S
+    DBuf m2l_key, m2l_key2, m2l_val, m2l_val2;    // u64 (class<<32|T; the plan's key when FP64), int32 S
     int64_t n_m2l = 0;
     std::vector<int64_t> class_beg, class_end;    // host: segments of the sorted m2l list per class
     std::vector<int32_t> class_used;
+    // M2L plan (lss_fmm.hip: m2l_plan): pairs sorted by (block of 2^m2l_shift
+    // target boxes, rank of the class, box), tiles of pairs, pairs per box
+    int m2l_shift = 0;
+    DBuf m2l_tab;                                 // per class: rank; per rank: group, angle and reflection
+    DBuf m2l_flag, m2l_pos, m2l_ts, m2l_meta;     // tile heads; used groups, block offsets
+    DBuf m2l_csr_key, m2l_csr_key2, m2l_csr, m2l_csr2, m2l_beg, m2l_end;   // pair indices by target box
+    std::vector<int64_t> m2l_blk;                 // host: first pair of each block
+    std::vector<int32_t> m2l_blk_tile;            // and its first tile
+    std::vector<int32_t> m2l_used;                // groups with pairs
     // expansions and operators
     int p = 0, ncp = 0, K = 4;
     DBuf M, L, L2;                            // nboxes * ncp doubles (L2: the M2L classes of the second stream)
@@ -225,6 +234,12 @@ struct Tree {
     DBuf opM2M, opL2L, opM2L;                 // 8, 8 and nclass_used operators (ncp*ncp, k-major)
     std::vector<int32_t> op_class_slot;       // class -> slot in opM2L (-1 if not built)
     int ops_p = -1, ops_R = -1;
+    // FP64 M2L: operators in use, rotation and index tables, slot and order per group
+    DBuf opM2G, m2l_trig, m2l_qtab, m2l_grp;
+    DBuf m2l_y, m2l_tmp, m2l_bsum;            // products of one block of pairs; sort and compaction workspace
+    std::vector<int32_t> op_group_slot;       // group -> slot in opM2G (-1 if not built)
+    int m2l_p = -1;                           // order of these tables and operators
+    std::vector<int32_t> h_m2l_grp;           // host copy of m2l_grp (the upload is asynchronous)
     // frontier scratch
     DBuf fr, fr2, cnt;
     // target-side cut radius per box (built with Ctx::target_widths)
@@ -370,11 +385,9 @@ void launch_newton_output(Ctx &c, int64_t N, double *h, double *xout, int8_t *st
 inline int fmm_order_for(const Ctx &c) {
     return c.opt.fmm_order > 0 ? c.opt.fmm_order : (c.opt.precision == LSS_MIXED ? 20 : 26);
 }
-void build_tree(Ctx &c);
-// the two halves of build_tree: the boxes (levels, radii, target cuts), then
-// the interaction lists of the dual traversal (sorted, per class)
+// the boxes (levels, radii, target cuts), then the interaction lists
 void build_tree_boxes(Ctx &c);
-void build_tree_lists(Ctx &c);     // traversal and the sorted M2L list
+void build_tree_lists(Ctx &c);     // dual traversal; mixed: the M2L list sorted by class
 void sort_near_lists(Ctx &c);      // the sorted direct and M2P lists, per-box tile costs
 void build_fmm(Ctx &c);
 void launch_locate_targets(Ctx &c, int64_t n_max, const int32_t *n_dev, const double *tx, const double *ty,

@@ -890,8 +890,14 @@ void build_tree_lists(Ctx &c) {
         std::swap(t.fr.bytes, t.fr2.bytes);
         nfr = npush;
     }
-    // the M2L list sorted by class; the direct and M2P lists are sorted by
-    // sort_near_lists (the translations do not need them)
+    c.stats.n_boxes = t.nboxes;
+    c.stats.tree_depth = t.depth;
+    c.stats.n_m2l = t.n_m2l;
+    c.stats.n_m2p = t.n_m2p;
+    // the direct and M2P lists are sorted by sort_near_lists (the translations
+    // do not need them), the M2L list of an FP64 context by m2l_plan; the
+    // mixed path's is sorted by class here
+    if (c.opt.precision != LSS_MIXED) return;
     t.m2l_key2.ensure(8 * (t.n_m2l + 1)); t.m2l_val2.ensure(4 * (t.n_m2l + 1));
     sort_pairs(c, t.m2l_key.as<uint64_t>(), t.m2l_key2.as<uint64_t>(), t.m2l_val.as<int32_t>(),
                t.m2l_val2.as<int32_t>(), t.n_m2l, 32 + bits_for(kNClass));
@@ -911,10 +917,6 @@ void build_tree_lists(Ctx &c) {
     t.class_used.clear();
     for (int k = 0; k < kNClass; ++k)
         if (t.class_end[k] > t.class_beg[k]) t.class_used.push_back(k);
-    c.stats.n_boxes = t.nboxes;
-    c.stats.tree_depth = t.depth;
-    c.stats.n_m2l = t.n_m2l;
-    c.stats.n_m2p = t.n_m2p;
 }
 
 // Direct and M2P lists sorted by target box (then source box), their
@@ -951,12 +953,6 @@ void sort_near_lists(Ctx &c) {
                        t.m2p_beg.as<int32_t>(), t.m2p_end.as<int32_t>(), (int64_t)(p_est + 2) * (p_est + 2) / 4,
                        t.nb.as<int64_t>(), t.ne.as<int64_t>(), t.near_cnt.as<int64_t>());
     LSS_CHECK_LAUNCH("k_near_count");
-}
-
-void build_tree(Ctx &c) {
-    build_tree_boxes(c);
-    build_tree_lists(c);
-    sort_near_lists(c);
 }
 
 void launch_soa(Ctx &c, const double *x, int64_t n, double *tx, double *ty, double *tz) {

@@ -57,3 +57,47 @@ def test_direct_split_matches_unsplit(prec):
     p1, g1 = c.eval(b["targets"][k], x_mesh=b["target_mesh"][k])
     tol = {lss.FP64: 1e-13, lss.MIXED: 1e-6}[prec]
     assert _err(p1, p0[k]) <= tol and _err(g1, g0[k]) <= tol
+
+
+def _forest(flip=lambda x: x):
+    """Two star surfaces and a cube too small for any translation, their coordinates mapped by `flip`."""
+    parts = [(star_surface(14, seed=5), 4000), (star_surface(9, seed=6), 1500), (cube_mesh(1), 100)]
+    return configs.concat_batch([dict(verts=flip(v), tris=t, sigma=0.12 * triangle_diameters(v, t),
+                                      targets=flip(bbox_targets(v, m, seed=m))) for (v, t), m in parts])
+
+
+@pytest.mark.parametrize("p,K", [(26, 7), (26, 18), (40, 8)])
+def test_m2l_against_direct(p, K):
+    """At orders whose truncation is below rounding the field of a ragged forest equals the exact sum (1e-12), and a
+    rebuild, which reuses the plan's buffers and operators, gives the same bits."""
+    b = _forest()
+    c = lss.Context()
+    c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+    c.set_sigma(b["sigma"])
+    p0, g0 = c.eval(b["targets"], x_mesh=b["target_mesh"])
+    c.set_options(far_field=lss.FAR_FMM, fmm_order=p, admissibility=K)
+    p1, g1 = c.eval(b["targets"], x_mesh=b["target_mesh"])
+    assert c.stats()["n_m2l"] > 1000
+    assert _err(p1, p0) <= 1e-12 and _err(g1, g0) <= 1e-12
+    c.set_sigma(b["sigma"])
+    p2, g2 = c.eval(b["targets"], x_mesh=b["target_mesh"])
+    assert np.array_equal(p1, p2) and np.array_equal(g1, g2)
+
+
+@pytest.mark.parametrize("p", [2, 3, 7, 11, 20, 26])
+def test_m2l_symmetry(p):
+    """A quarter turn about z and a reflection z -> -z map the octree onto itself and every displacement to another of
+    its group, and the series truncated at order p onto the truncated series: the field at the mapped targets is the
+    mapped field to rounding (1e-12 of the largest value, orders around the tile and padding sizes)."""
+    got = []
+    for turn in (lambda x: x, lambda x: np.stack([-x[:, 1], x[:, 0], -x[:, 2]], 1)):
+        b = _forest(turn)
+        b["tris"] = b["tris"] if not got else np.ascontiguousarray(b["tris"][:, ::-1])   # a reflection turns them over
+        c = lss.Context()
+        c.set_options(far_field=lss.FAR_FMM, fmm_order=p, leaf_capacity=32)
+        c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+        c.set_sigma(b["sigma"])
+        got.append(c.eval(b["targets"], x_mesh=b["target_mesh"]))
+    (p0, g0), (p1, g1) = got
+    assert _err(p1, p0) <= 1e-12
+    assert _err(np.stack([g1[:, 1], -g1[:, 0], -g1[:, 2]], 1), g0) <= 1e-12
