@@ -291,9 +291,10 @@ struct Ctx {
     DBuf tflag, tpos, tstart, ntiles, tleaf;   // FMM eval: leaf of each sorted target, tile heads
     DBuf pairs;               // double accumulator of executed pairs (stats)
     DBuf part;                // partial sums of a direct evaluation whose nodes are split
-    DBuf tile_queue;          // uint32[2] work queue of the FMM evaluation (zero between launches)
+    DBuf tile_queue;          // uint32[4] work queue of the FMM evaluation (zero between launches)
     DBuf tile_order;          // FMM tiles, most expensive first (int32 per tile)
-    DBuf tile_bucket;         // int32[2 * kCostBuckets]: bucket counts (zero between uses), offsets
+    DBuf tile_bucket;         // int32[2 * kCostBuckets + 1]: bucket counts (zero between uses), offsets,
+                              // heavy tiles
     bool pairs_pending = false;   // counter not yet read back into stats.last_pairs
     NewtonState ns;
 
@@ -408,9 +409,12 @@ void launch_soa(Ctx &c, const double *x, int64_t n, double *tx, double *ty, doub
 // Newton targets in FMM mode: leaf of each target in its current order and
 // tile heads at leaf changes and every TILE-th position (no sort; capturable)
 void ensure_tiles(Ctx &c, int64_t n_max);
-// tile order for the work queue: tiles bucketed by log2 of their direct-list
-// size, most expensive bucket first (kernels only: capturable)
-constexpr int kCostBuckets = 64;
+// tile order for the work queue: tiles bucketed by cost (near_cnt of their
+// leaf), four buckets per factor of two, most expensive bucket first (kernels
+// only: capturable)
+constexpr int kCostBuckets = 128;
+constexpr int kWide = 8;                  // most waves of an evaluation workgroup (for_tiles)
+constexpr int kWideWaves = 4096;          // waves resident on the chip (four per SIMD)
 void order_tiles(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const int32_t *tile_start,
                  const int32_t *leaf, int32_t *order);
 void build_tiles_unsorted(Ctx &c, int64_t n_max, const int32_t *n_dev, int tile);

@@ -772,10 +772,12 @@ struct FmmEvalArgs {
     const double *root;         // per-mesh root cubes (corner xyz, side)
     const int32_t *bmesh;
     double *pairs;
-    // tile queue: [0] next tile, [1] finished workgroups; zero between
-    // launches (the last workgroup to finish clears both)
+    // tile queue: [0] next tile, [1] finished workgroups; for_tiles: [2] next
+    // heavy tile, [3] finished workgroups; zero between launches (the last
+    // workgroup to finish clears them)
     unsigned int *queue;
     const int32_t *order;       // queue position -> tile (most expensive first)
+    const int32_t *nheavy;      // tiles at the front of the order that a whole workgroup takes (for_tiles)
 };
 
 // next tile for the workgroup (uniform); tiles are handed out in list order
@@ -1353,6 +1355,9 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int64_t n = a.n_dev ? (int64_t)*a.n_dev : a.n_max;
     const int lane = threadIdx.x;
     __shared__ int slot;
+    // uniform over the grid: the queue is not touched (a launch without targets,
+    // as the last iterations of a captured projection are, took 430 us)
+    if (ntiles <= 0) return;
     for (int q = next_tile(a, &slot); q < ntiles; q = next_tile(a, &slot)) {
         const int tile = a.order[q];
         const int64_t s0 = a.tile_start[tile];
@@ -1424,87 +1429,225 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
 }
 
 
-// FP64 path with 64-target tiles: as the mixed kernel below, every staged
-// node is tested against the tile's target bounding box and goes to the near
-// ring (the general loop: the far form for every pair, the rational fit for
-// node groups with a pair inside the cut) or to the far ring (the dipole-only
-// loop).  Nodes are staged 32 at a time, so that the two rings (7 KB) leave
-// room for the 16 workgroups of four waves per SIMD in a CU's LDS.
-constexpr int kNodeGroupSplit = 2;       // node group of the split kernel (fewer registers than 4)
+// ------------------------------------------------------- workgroups of waves
+// The FP64 evaluation kernels run persistent workgroups of up to kWide waves.
+// First the workgroups take the heavy tiles (k_tile_bucket_scan) one by one:
+// the waves share a tile's direct list chunk by chunk and its M2P boxes, each
+// with staging and totals of its own, and add the totals in wave order at the
+// end; there is no other barrier.  Then every wave takes light tiles by
+// itself.  One wave alone on a SIMD issues about every fifth cycle that it
+// could (FP64 latency), so a tile of many times the usual cost, on one wave,
+// outlasts everything else: on 2e5 graded triangles a dozen of 40 000 tiles
+// hold 1e5 to 4e5 nodes and hundreds of M2P boxes where a usual one has 1e4.
+// FP64 evaluation, before with one wave per tile and after: 77 760 chart nodes
+// 4.1 -> 1.8 ms (floor of the VALU issue 0.9), 4.7e5 chart nodes 26 -> 12.6
+// (9.1), 2e6 targets on 2e5 triangles 117 -> 70 (56).
+
+// LDS between lanes of one wave: orders the accesses, no barrier
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// up to 64 node ranges of a direct list, packed one after the other
+struct RangeList {
+    int64_t beg[64];
+    int32_t off[65];
+};
+
+// ranges [e, e + nr), nr <= 64, of the direct list, by one wave; returns the
+// packed length (64 boxes hold fewer than 2^31 nodes)
+__device__ __forceinline__ int wave_ranges(const FmmEvalArgs &a, RangeList &rl, int e, int nr) {
+    const int t = threadIdx.x & 63;
+    int len = 0;
+    wave_sync();                            // the previous batch is done with
+    if (t < nr) {
+        const int32_t S = a.p2p_src[e + t];
+        rl.beg[t] = a.nb[S];
+        len = (int)(a.ne[S] - a.nb[S]);
+    }
+    for (int d = 1; d < 64; d <<= 1) {
+        const int v = __shfl_up(len, d);
+        if (t >= d) len += v;
+    }
+    rl.off[t + 1] = len;
+    if (t == 0) rl.off[0] = 0;
+    wave_sync();
+    return rl.off[nr];
+}
+
+// node index of packed position v (v < total)
+__device__ __forceinline__ int64_t range_node(const RangeList &rl, int nr, int v) {
+    int lo = 0, hi = nr;                       // last r with off[r] <= v
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (rl.off[mid] <= v) lo = mid; else hi = mid;
+    }
+    return rl.beg[lo] + (v - rl.off[lo]);
+}
+
+// bounding box of the wave's targets, lanes past the tile end holding its
+// first (lo in box[0..2], hi in box[3..5])
+__device__ __forceinline__ void wave_box(double x, double y, double z, double *box) {
+    double lo[3] = {x, y, z}, hi[3] = {x, y, z};
+    for (int off = 32; off > 0; off >>= 1)
+        for (int c = 0; c < 3; ++c) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off));
+        }
+    wave_sync();
+    if ((threadIdx.x & 63) == 0)
+        for (int c = 0; c < 3; ++c) {
+            box[c] = lo[c];
+            box[3 + c] = hi[c];
+        }
+    wave_sync();
+}
+
+// squared distance of (x, y, z) from the box
+__device__ __forceinline__ double box_gap2(const double *box, double x, double y, double z) {
+    const double gx = fmax(fmax(box[0] - x, x - box[3]), 0.0);
+    const double gy = fmax(fmax(box[1] - y, y - box[4]), 0.0);
+    const double gz = fmax(fmax(box[2] - z, z - box[5]), 0.0);
+    return gx * gx + gy * gy + gz * gz;
+}
+
+// scaled position of (x, y, z) in box S, and 1 / its side
+__device__ __forceinline__ void box_position(const FmmEvalArgs &a, int32_t S, double x, double y, double z, double r[3],
+                                             double &inv) {
+    const double s = box_side(a.root, a.bmesh, S, a.lev[S]);
+    const double *o = a.root + 4 * a.bmesh[S];
+    inv = 1.0 / s;
+    r[0] = (x - (o[0] + (a.ijk[3 * S] + 0.5) * s)) * inv;
+    r[1] = (y - (o[1] + (a.ijk[3 * S + 1] + 0.5) * s)) * inv;
+    r[2] = (z - (o[2] + (a.ijk[3 * S + 2] + 0.5) * s)) * inv;
+}
+
+// expansion of box S into the wave's buffer
+__device__ __forceinline__ void wave_stage(const double *src, int ncp, double *buf) {
+    wave_sync();
+    for (int k = threadIdx.x & 63; k < ncp; k += 64) buf[k] = src[k];
+    wave_sync();
+}
+
+// Tile loop of such a kernel: tile(t, W, w) for the heavy tiles with all the
+// W waves of a workgroup (w: this wave), then tile(t, 1, 0) wave by wave.
+// queue[2], queue[3]: next heavy tile, finished workgroups; queue[0]: next
+// light tile; cleared by the last workgroup.  A launch without tiles returns
+// at once (uniform over the grid).
+template <class F>
+__device__ __forceinline__ void for_tiles(const FmmEvalArgs &a, int *slot, F tile) {
+    const int ntiles = *a.ntiles_dev, heavy = min(*a.nheavy, ntiles);
+    if (ntiles <= 0) return;
+    const int waves = (int)(blockDim.x >> 6), self = (int)(threadIdx.x >> 6);
+    // one loop for both phases: two copies of the tile code would compete for
+    // the instruction cache while some workgroups are in either
+    for (bool together = heavy > 0;;) {
+        int q = 0;
+        if (together) {
+            __syncthreads();                // everyone has read the slot and left the totals
+            if (threadIdx.x == 0) *slot = (int)atomicAdd(a.queue + 2, 1u);
+            __syncthreads();
+            q = *slot;
+            if (q >= heavy) {
+                together = false;
+                continue;
+            }
+        } else {
+            if ((threadIdx.x & 63) == 0) q = (int)atomicAdd(a.queue, 1u);
+            q = heavy + __builtin_amdgcn_readfirstlane(q);
+            if (q >= ntiles) break;
+        }
+        tile(a.order[q], together ? waves : 1, together ? self : 0);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(a.queue + 3, 1u) == gridDim.x - 1) {
+            atomicExch(a.queue, 0u);
+            atomicExch(a.queue + 2, 0u);
+            atomicExch(a.queue + 3, 0u);
+        }
+    }
+}
+
+// Static LDS per wave of such a kernel, and the waves of a workgroup whose
+// staging regions (rings, then one expansion, then totals) fit 64 KiB
+struct WaveLds {
+    RangeList rl;
+    double box[7];
+};
+inline int waves_for(size_t region) {
+    const size_t n = (64 * 1024 - 64 - kWide * sizeof(WaveLds)) / region;
+    return (int)(n < 1 ? 1 : (n > (size_t)kWide ? kWide : n));
+}
+inline size_t region_for(size_t rings, int ncp) {
+    return (std::max(rings, sizeof(double) * (size_t)ncp) + 15) & ~(size_t)15;
+}
+
+// FP64 evaluation.  Every staged node is tested against the tile's target
+// bounding box and goes to the near ring (the general loop: the far form for
+// every pair, the rational fit for node groups with a pair inside the cut) or
+// to the far ring (the dipole-only loop).  Nodes are staged 32 at a time, so
+// that the two rings (7 KB) leave room for four waves per SIMD in a CU's LDS.
+// Bound by FP64 VALU issue; four waves per SIMD (128 VGPRs, a few spills
+// outside the pair loops).  COUNT: also count the pairs inside the cut
+// (pairs[2]) and those of the dipole-only loop (pairs[3]), for the statistics.
+constexpr int kNodeGroupSplit = 2;       // node group (fewer registers than 4)
 constexpr int kRun64 = 32;               // records per partial sum
 constexpr int kRing64 = 64;              // kRun64 - 1 left over + 32 staged
 
 constexpr size_t kF64RingBytes = kRing64 * (sizeof(Src) + sizeof(FarD));
 
 template <bool COUNT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_fmm_f64_split(FmmEvalArgs a) {
-    constexpr int W = 64;
-    __shared__ RangeBatch<W> rb;
-    __shared__ double tbox[6];          // the tile's target bounding box
-    // node rings while the pairs run, then the local expansion (ncp doubles)
-    // and the M2P staging buffer
+__global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_fmm_f64_waves(FmmEvalArgs a,
+                                                                                                      int region_doubles) {
+    __shared__ WaveLds wl[kWide];
+    __shared__ int slot;
     extern __shared__ __attribute__((aligned(16))) double Ls[];
-    Src *ring_n = reinterpret_cast<Src *>(Ls);
+    const int lane = threadIdx.x & 63, self = threadIdx.x >> 6;
+    double *region = Ls + region_doubles * self, *box = wl[self].box;
+    RangeList &rl = wl[self].rl;
+    Src *ring_n = reinterpret_cast<Src *>(region);
     FarD *ring_f = reinterpret_cast<FarD *>(ring_n + kRing64);
     const int ntiles = *a.ntiles_dev;
     const int64_t n = a.n_dev ? (int64_t)*a.n_dev : a.n_max;
-    const int lane = threadIdx.x;
     const double far_u = KF64_X * (1.0 + 1e-6);
-    __shared__ int slot;
-    for (int q = next_tile(a, &slot); q < ntiles; q = next_tile(a, &slot)) {
-        const int tile = a.order[q];
+    for_tiles(a, &slot, [&](int tile, int W, int w) {
         const int64_t s0 = a.tile_start[tile];
         const int32_t B = a.sleaf[s0];
-        if (B >= a.nboxes) continue;        // outside the root cube: k_eval_outside
+        if (B >= a.nboxes) return;          // outside the root cube: k_eval_outside
         const int64_t s1 = tile + 1 < ntiles ? (int64_t)a.tile_start[tile + 1] : n;   // tile = [s0, s1)
         const int64_t sp_ = s0 + lane;
         const bool valid = sp_ < s1;
         const int64_t ti = a.sidx ? (int64_t)a.sidx[valid ? sp_ : s0] : (valid ? sp_ : s0);
         const double x = a.tx[ti], y = a.ty[ti], z = a.tz[ti];
-        const int e0 = a.p2p_beg[B], e1 = a.p2p_end[B];
-        {
-            double blo[3] = {x, y, z}, bhi[3] = {x, y, z};      // lanes past the tile end hold its first target
-            for (int off = 32; off > 0; off >>= 1)
-                for (int c = 0; c < 3; ++c) {
-                    blo[c] = fmin(blo[c], __shfl_xor(blo[c], off));
-                    bhi[c] = fmax(bhi[c], __shfl_xor(bhi[c], off));
-                }
-            __syncthreads();                // the previous tile is done with tbox
-            if (lane == 0)
-                for (int c = 0; c < 3; ++c) {
-                    tbox[c] = blo[c];
-                    tbox[3 + c] = bhi[c];
-                }
-        }
+        wave_box(x, y, z, box);
+        const int e1 = a.p2p_end[B];
         double sp = 0, ep = 0, sx = 0, ex = 0, sy = 0, ey = 0, sz = 0, ez = 0;
         double npair = 0.0, nfar = 0.0;
         uint32_t nuse = 0;
-        int hn = 0, nn = 0, hf = 0, nf = 0;     // head and fill of each ring (uniform)
-        int eb = e0, nr = 0;
-        int64_t total = 0, c0 = 0;
+        int hn = 0, nn = 0, hf = 0, nf = 0;     // head and fill of the wave's rings (uniform)
+        int eb = a.p2p_beg[B], nr = 0, total = 0, c0 = 0;
         for (bool last = false; !last;) {
             while (c0 >= total && eb < e1) {    // next batch of the leaf's direct list
-                nr = e1 - eb < W ? e1 - eb : W;
-                __syncthreads();
-                total = load_ranges<W>(a, rb, eb, nr);
+                nr = e1 - eb < 64 ? e1 - eb : 64;
+                total = wave_ranges(a, rl, eb, nr);
                 npair += (double)total;
-                c0 = 0;
+                c0 = w * kRun64;
                 eb += nr;
             }
             last = c0 >= total;             // every node is staged: pad the remainders
-            const int cnt = last ? 0 : (int)(total - c0 < kRun64 ? total - c0 : kRun64);
+            const int cnt = last ? 0 : (total - c0 < kRun64 ? total - c0 : kRun64);
             Src sr;
             bool isfar = false;
             if (lane < cnt) {
-                sr = a.src[packed_node<W>(rb, nr, c0 + lane)];
-                const double gx_ = fmax(fmax(tbox[0] - sr.yx, sr.yx - tbox[3]), 0.0);
-                const double gy_ = fmax(fmax(tbox[1] - sr.yy, sr.yy - tbox[4]), 0.0);
-                const double gz_ = fmax(fmax(tbox[2] - sr.yz, sr.yz - tbox[5]), 0.0);
-                isfar = (gx_ * gx_ + gy_ * gy_ + gz_ * gz_) * sr.s2 >= far_u;
+                sr = a.src[range_node(rl, nr, c0 + lane)];
+                isfar = box_gap2(box, sr.yx, sr.yy, sr.yz) * sr.s2 >= far_u;
             }
-            c0 += cnt;
+            c0 += W * kRun64;
             const uint64_t fm = __ballot(isfar), nm = __ballot(lane < cnt && !isfar);
-            __syncthreads();                // the runs taken last are read
+            wave_sync();                    // the runs taken last are read
             if (lane < cnt && !isfar) {
                 int pos = hn + nn + below(nm);
                 if (pos >= kRing64) pos -= kRing64;
@@ -1534,7 +1677,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 if (lane >= nn && lane < ln) ring_n[hn + lane] = pad_src();
                 if (lane >= nf && lane < lf) ring_f[hf + lane] = pad_fard();
             }
-            __syncthreads();
+            wave_sync();
             if (ln > 0) {
                 double p = 0, gx = 0, gy = 0, gz = 0;
 #pragma unroll 1
@@ -1563,18 +1706,51 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 nf = nf > kRun64 ? nf - kRun64 : 0;
             }
         }
-        double ph = 0.0, g[3] = {0.0, 0.0, 0.0}, mph = 0.0, mg[3] = {0.0, 0.0, 0.0};
-        if (a.m2p_end[B] > a.m2p_beg[B])    // uniform: Ls is the M2P staging buffer first
-            fmm_m2p_list(a, B, Ls, x, y, z, mph, mg);
-        __syncthreads();                    // the rings (or the M2P buffer) are done
-        stage_local(a, B, Ls);
-        __syncthreads();                    // Ls staged
-        fmm_l2p(a, B, Ls, x, y, z, ph, g);
-        ph += mph;
-        g[0] += mg[0];
-        g[1] += mg[1];
-        g[2] += mg[2];
-        if (valid) {
+        // expansions, one at a time in the wave's region: its share of the M2P
+        // list, and for the last wave the local expansion
+        double ph = 0.0, g[3] = {0.0, 0.0, 0.0};
+        const int m1 = a.m2p_end[B];
+        for (int e = a.m2p_beg[B] + w; e < m1; e += W) {
+            const int32_t S = a.m2p_src[e];
+            wave_stage(a.M + (int64_t)S * a.ncp, a.ncp, region);
+            double r[3], inv, p1, g1[3];
+            box_position(a, S, x, y, z, r, inv);
+            fmm::m2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
+            ph += p1;
+            for (int c = 0; c < 3; ++c) g[c] += g1[c];
+        }
+        if (w == W - 1) {
+            wave_stage(a.L + (int64_t)B * a.ncp, a.ncp, region);
+            double r[3], inv, p1, g1[3];
+            box_position(a, B, x, y, z, r, inv);
+            fmm::l2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
+            ph += p1;
+            for (int c = 0; c < 3; ++c) g[c] += g1[c];
+        }
+        if (W > 1) {                        // the waves' totals: sum, error term and far field of component c
+            __syncthreads();                // every wave is done with its region
+            const double ts[4] = {sp, sx, sy, sz}, te[4] = {ep, ex, ey, ez}, tf[4] = {ph, g[0], g[1], g[2]};
+            for (int c = 0; c < 4; ++c) {
+                double *t = Ls + (w * 4 + c) * 192 + lane;
+                t[0] = ts[c];
+                t[64] = te[c];
+                t[128] = tf[c];
+            }
+            __syncthreads();
+            for (int c = w; c < 4 && valid; c += W) {
+                double s = 0.0, e = 0.0, f = 0.0;
+                for (int v = 0; v < W; ++v) {
+                    const double *t = Ls + (v * 4 + c) * 192 + lane;
+                    two_sum(s, e, t[0]);
+                    e += t[64];
+                    f += t[128];
+                }
+                const int64_t o = a.out_idx ? (int64_t)a.out_idx[ti] : ti;
+                const double v = (s + f) + e;
+                if (c == 0) a.phi[o] = v;
+                else if (a.grad) a.grad[3 * o + c - 1] = v;
+            }
+        } else if (valid) {
             const int64_t o = a.out_idx ? (int64_t)a.out_idx[ti] : ti;
             a.phi[o] = (sp + ph) + ep;
             if (a.grad) {
@@ -1585,20 +1761,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         }
         if (a.pairs) {                      // [0] pairs of real targets, [1] lane slots spent, [2] inside the cut,
                                             // [3] taken by the dipole-only loop
-            const double w = wave_sum(valid ? npair : 0.0), wl = wave_sum(npair);
             const double wu = COUNT ? wave_sum(valid ? (double)nuse : 0.0) : 0.0;
             const double wf = COUNT ? wave_sum(valid ? nfar : 0.0) : 0.0;
             if (lane == 0) {
-                atomicAdd(a.pairs, w);
-                atomicAdd(a.pairs + 1, wl);
+                if (w == 0) {               // every wave counts the whole list
+                    atomicAdd(a.pairs, (double)(s1 - s0) * npair);
+                    atomicAdd(a.pairs + 1, 64.0 * npair);
+                }
                 if (COUNT) {
                     atomicAdd(a.pairs + 2, wu);
                     atomicAdd(a.pairs + 3, wf);
                 }
             }
         }
-    }
-    queue_done(a);
+    });
 }
 
 // Mixed path: one wavefront per tile of 64 targets.  Each staged node is
@@ -1630,6 +1806,9 @@ __global__ __launch_bounds__(64) void k_eval_fmm_mixed(FmmEvalArgs a) {
     const int lane = threadIdx.x;
     const double far_u = (double)KF32_X * (1.0 + 1e-4);     // margin over the FP32 rounding of u
     __shared__ int slot;
+    // uniform over the grid: the queue is not touched (a launch without targets,
+    // as the last iterations of a captured projection are, took 430 us)
+    if (ntiles <= 0) return;
     for (int q = next_tile(a, &slot); q < ntiles; q = next_tile(a, &slot)) {
         const int tile = a.order[q];
         const int64_t s0 = a.tile_start[tile];
@@ -1849,17 +2028,18 @@ void launch_hess_tile(Ctx &c, unsigned grid, const FmmEvalArgs &a, double *hess)
     LSS_CHECK_LAUNCH("k_hess_fmm");
 }
 
+// persistent workgroups of waves: two of kWide waves fill a CU at 128 VGPRs
+void launch_f64_waves(Ctx &c, int64_t max_tiles, const FmmEvalArgs &a) {
+    const size_t region = region_for(kF64RingBytes, a.ncp);
+    const int W = waves_for(region);
+    const unsigned grid = (unsigned)std::min<int64_t>(max_tiles > 0 ? max_tiles : 1, kWideWaves / W);
+    auto k = c.opt.count_useful ? k_eval_fmm_f64_waves<true> : k_eval_fmm_f64_waves<false>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * W), region * W, c.stream, a, (int)(region / sizeof(double)));
+    LSS_CHECK_LAUNCH("k_eval_fmm_f64_waves");
+}
+
 template <int TILE>
 void launch_fmm_tile(Ctx &c, unsigned grid, const FmmEvalArgs &a) {
-    if (TILE == 64) {
-        const size_t shm = std::max(kF64RingBytes, sizeof(double) * (size_t)a.ncp);
-        if (c.opt.count_useful)
-            hipLaunchKernelGGL(k_eval_fmm_f64_split<true>, dim3(grid), dim3(64), shm, c.stream, a);
-        else
-            hipLaunchKernelGGL(k_eval_fmm_f64_split<false>, dim3(grid), dim3(64), shm, c.stream, a);
-        LSS_CHECK_LAUNCH("k_eval_fmm_f64_split");
-        return;
-    }
     const size_t shm = sizeof(double) * (size_t)a.ncp;
     if (c.opt.count_useful)
         hipLaunchKernelGGL((k_eval_fmm_f64<TILE, true>), dim3(grid), dim3(TILE), shm, c.stream, a);
@@ -1916,6 +2096,7 @@ void launch_eval_fmm(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const
     a.pairs = pairs;
     a.queue = c.tile_queue.as<unsigned int>();
     a.order = order;
+    a.nheavy = c.tile_bucket.as<int32_t>() + 2 * kCostBuckets;
     a.child = t.child.as<int32_t>();
     a.parent = t.parent.as<int32_t>();
     a.rmax = t.rmax.as<double>();
@@ -1961,7 +2142,7 @@ void launch_eval_fmm(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const
         LSS_CHECK_LAUNCH("k_eval_fmm_mixed");
     } else {
         switch (fmm_tile(c)) {
-            case 64: launch_fmm_tile<64>(c, grid, a); break;
+            case 64: launch_f64_waves(c, max_tiles, a); break;
             case 128: launch_fmm_tile<128>(c, grid, a); break;
             default: launch_fmm_tile<256>(c, grid, a); break;
         }

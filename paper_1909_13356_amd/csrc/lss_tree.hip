@@ -548,7 +548,7 @@ __global__ void k_tile_flags_runs(int64_t n_max, const int32_t *__restrict__ n_d
 }
 
 // cost of a target of every box, in node pairs: the nodes on its direct list
-// plus m2p_weight per M2P box; and of every mesh's outside range
+// plus m2p_weight per M2P box
 __global__ void k_near_count(int64_t nboxes, int32_t nmesh, const int32_t *__restrict__ beg,
                              const int32_t *__restrict__ end, const int32_t *__restrict__ src,
                              const int32_t *__restrict__ mbeg, const int32_t *__restrict__ mend, int64_t m2p_weight,
@@ -559,14 +559,19 @@ __global__ void k_near_count(int64_t nboxes, int32_t nmesh, const int32_t *__res
         for (int32_t e = beg[b]; e < end[b]; ++e) s += ne[src[e]] - nb[src[e]];
         cnt[b] = s + m2p_weight * (int64_t)(mend[b] - mbeg[b]);
     } else if (b < nboxes + nmesh) {
-        const int64_t m = b - nboxes;
-        cnt[b] = ne[m] - nb[m];
+        cnt[b] = 0;                      // outside a root cube: not the tile kernels' work
     }
 }
 
-__device__ inline int cost_bucket(int64_t c) {           // 0 = most expensive
-    const int lg = c > 0 ? 63 - __clzll((unsigned long long)c) : 0;
-    return kCostBuckets - 1 - lg;
+// 4 buckets per factor of two, 0 = most expensive; and a bucket's middle cost
+__device__ inline int cost_bucket(int64_t c) {
+    if (c < 4) return kCostBuckets - 1;
+    const int lg = 63 - __clzll((unsigned long long)c);
+    return max(kCostBuckets - 1 - (4 * lg + (int)((c >> (lg - 2)) & 3)), 0);
+}
+__device__ inline double bucket_cost(int b) {
+    const int k = kCostBuckets - 1 - b;
+    return ldexp(1.125 + 0.25 * (k & 3), k >> 2);
 }
 
 // grid-stride over the tiles (their count is on the device); per-block LDS
@@ -585,16 +590,43 @@ __global__ void k_tile_bucket_count(int64_t max_tiles, const int32_t *__restrict
         if (h[i]) atomicAdd(&bucket[i], h[i]);
 }
 
-// single block: offsets from the counts, counts cleared for the next use
-__global__ void k_tile_bucket_scan(int32_t *bucket) {
-    if (threadIdx.x == 0) {
-        int32_t s = 0;
-        for (int i = 0; i < kCostBuckets; ++i) {
-            bucket[kCostBuckets + i] = s;
-            s += bucket[i];
-            bucket[i] = 0;
-        }
+// single block: offsets from the counts, counts cleared for the next use, and
+// how many of the first (most expensive) tiles are heavy: a whole workgroup
+// takes each of them (for_tiles in lss_p2p.hip).  The line: a cost of at least
+// 1 / kHeavyShare of what each of the chip's resident waves gets, so that the
+// tiles that single waves take end within an eighth of the launch of each
+// other.  At 1/4, 4.7e5 chart nodes left little more than one round of light
+// tiles, each a quarter of the launch long: 16.0 ms an evaluation against 12.6
+// at 1/8 and 13.0 at 1/2; 2e6 targets (40 000 tiles): 70 ms with any.
+constexpr double kHeavyShare = 8.0;
+__global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket) {
+    constexpr int kPer = kCostBuckets / 64;
+    const int lane = threadIdx.x;
+    int32_t n[kPer], s = 0;
+    double total = 0.0;
+    for (int k = 0; k < kPer; ++k) {
+        const int i = kPer * lane + k;
+        n[k] = bucket[i];
+        bucket[i] = 0;
+        s += n[k];
+        total += n[k] * bucket_cost(i);
     }
+    int32_t at = s;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t v = __shfl_up(at, d);
+        if (lane >= d) at += v;
+        total += __shfl_xor(total, d);
+    }
+    at -= s;                                            // tiles of the lanes below
+    int32_t heavy = 0;
+    for (int k = 0; k < kPer; ++k) {
+        const int i = kPer * lane + k;
+        bucket[kCostBuckets + i] = at;
+        at += n[k];
+        if (bucket_cost(i) * kWideWaves * kHeavyShare >= total) heavy = at;
+    }
+    for (int d = 32; d > 0; d >>= 1) heavy = max(heavy, __shfl_xor(heavy, d));
+    if (lane == 0) bucket[2 * kCostBuckets] = heavy;
 }
 
 __global__ void k_tile_bucket_scatter(int64_t max_tiles, const int32_t *__restrict__ ntiles_dev,

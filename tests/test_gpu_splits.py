@@ -101,3 +101,30 @@ def test_m2l_symmetry(p):
     (p0, g0), (p1, g1) = got
     assert _err(p1, p0) <= 1e-12
     assert _err(np.stack([g1[:, 1], -g1[:, 0], -g1[:, 2]], 1), g0) <= 1e-12
+
+
+@pytest.mark.parametrize("prec", [lss.FP64, lss.MIXED])
+@pytest.mark.parametrize("n", [1, 65, 3000, 150_000])
+def test_fmm_tiles_shared_by_waves(n, prec):
+    """The octree evaluation with few tiles (every tile heavy: a workgroup each), and with enough that light tiles go to
+    single waves, on a ragged pair of surfaces with targets inside and outside the root cubes: the exact sum to the
+    precision's bar, and the same bits on a second call."""
+    parts = [star_surface(13, seed=3), star_surface(6, seed=4)]
+    meshes = [dict(verts=v, tris=t, sigma=0.5 * triangle_diameters(v, t),
+                   targets=bbox_targets(v, m, pad=p, seed=m)) for (v, t), m, p in zip(parts, (n, n // 3 + 1), (0.1, 3.0))]
+    b = configs.concat_batch(meshes)
+    c = lss.Context()
+    c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+    c.set_sigma(b["sigma"])
+    c.set_options(precision=prec, far_field=lss.FAR_FMM)
+    x, xm = b["targets"], b["target_mesh"]
+    p1, g1 = c.eval(x, x_mesh=xm)
+    p2, g2 = c.eval(x, x_mesh=xm)
+    assert np.array_equal(p1, p2) and np.array_equal(g1, g2)
+    k = np.unique(np.linspace(0, len(x) - 1, 3000).astype(int))
+    c.set_options(precision=lss.FP64)
+    p0, g0 = c.eval(x[k], x_mesh=xm[k])
+    # |Phi| <= 1 inside and the gradient reaches 1 / (sqrt(2 pi) sigma) at the surface: the natural scales, also for
+    # few targets far from it
+    scale = 1.0 / (np.sqrt(2.0 * np.pi) * b["sigma"].max())
+    assert np.abs(p1[k] - p0).max() <= BAR[prec] and np.abs(g1[k] - g0).max() <= BAR[prec] * scale
