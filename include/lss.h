@@ -160,9 +160,9 @@ typedef struct lss_stats {
                                  Newton step and compaction together) */
     int32_t pair_kernel_launches;  /* lss_eval: pair-kernel launches timed in pair_kernel_ms;
                                       lss_project: timed launches of Newton iterations (graphs of
-                                      8 iterations; with LSS_FAR_FMM the first iteration runs on
-                                      its own, and the active list is re-ordered by leaf before
-                                      every graph launch) */
+                                      4 iterations; with LSS_FAR_FMM the first iteration runs on
+                                      its own, and the active list is re-ordered by leaf after it
+                                      and after every 8 iterations) */
     int32_t pad0;
     double  lane_pairs;       /* pair evaluations the pair kernels spent, idle lanes of partly
                                  filled tiles included (last_pairs / lane_pairs = lane use) */

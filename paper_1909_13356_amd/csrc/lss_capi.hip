@@ -366,7 +366,9 @@ hipGraphExec_t capture_newton(Ctx &c, int64_t N, double tau, double *phi, double
     return exec;
 }
 
-constexpr int kNewtonChunk = 8;   // iterations per graph launch between host checks
+constexpr int kNewtonChunk = 8;   // iterations between re-orderings of the active list
+constexpr int kNewtonGraph = 4;   // iterations per graph launch between host checks (most projections
+                                  // need three or four: longer graphs end in empty iterations)
 
 // Everything the captured iterations bake in: the address of every buffer
 // their kernels touch, the sizes and scalars passed by value, and the options
@@ -422,7 +424,8 @@ void project(Ctx &c, const double *uv, int32_t np, double *h, double *xout, int8
     // empty launches and the host only checks the count between chunks.  The
     // chunk is captured once and relaunched by later calls whose key matches.
     const bool fmm = c.opt.far_field == LSS_FAR_FMM;
-    const int chunk = std::min(maxit, kNewtonChunk);
+    const int rebin = std::min(maxit, kNewtonChunk);
+    const int chunk = rebin % kNewtonGraph == 0 ? kNewtonGraph : rebin;
     std::vector<uint64_t> key = newton_key(c, N, tau, maxit, chunk);
     if (!s.exec || key != s.exec_key) {
         drop_newton_graph(s);
@@ -432,19 +435,23 @@ void project(Ctx &c, const double *uv, int32_t np, double *h, double *xout, int8
     hipGraphExec_t exec = s.exec;
     c.ev_reset();
     try {
-        int done = 0;
+        int done = 0, binned = 0;
         if (fmm && maxit > 1) {     // first step from the chart points, then re-bin by leaf
             c.ev_begin();
             newton_iteration(c, N, tau, phi.as<double>(), grad.as<double>());
             c.ev_end();
             done = 1;
+            binned = 1 - rebin;
         }
         for (; done < maxit; done += chunk) {
             int32_t nact = 0;
             LSS_HIP(hipMemcpyAsync(&nact, s.nact.p, sizeof(int32_t), hipMemcpyDeviceToHost, c.stream));
             LSS_HIP(hipStreamSynchronize(c.stream));
             if (nact == 0) break;
-            if (fmm && done > 0) rebin_active(c, N, nact);
+            if (fmm && done > 0 && done - binned >= rebin) {
+                rebin_active(c, N, nact);
+                binned = done;
+            }
             c.ev_begin();
             LSS_HIP(hipGraphLaunch(exec, c.stream));
             c.ev_end();
