@@ -414,6 +414,7 @@ void ensure_tiles(Ctx &c, int64_t n_max);
 // only: capturable)
 constexpr int kCostBuckets = 128;
 constexpr int kWide = 8;                  // most waves of an evaluation workgroup (for_tiles)
+constexpr int kHessWaves = 4;              // and of the Hessian and sigma(x) evaluations
 constexpr int kWideWaves = 4096;          // waves resident on the chip (four per SIMD)
 void order_tiles(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const int32_t *tile_start,
                  const int32_t *leaf, int32_t *order);

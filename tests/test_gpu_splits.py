@@ -128,3 +128,24 @@ def test_fmm_tiles_shared_by_waves(n, prec):
     # few targets far from it
     scale = 1.0 / (np.sqrt(2.0 * np.pi) * b["sigma"].max())
     assert np.abs(p1[k] - p0).max() <= BAR[prec] and np.abs(g1[k] - g0).max() <= BAR[prec] * scale
+
+
+@pytest.mark.parametrize("n", [1, 63, 2500, 60_000])
+def test_hessian_and_multiscale_tiles_shared_by_waves(n):
+    """The Hessian and the target-attached width through the octree against their every-pair paths, for few targets (a
+    workgroup per tile) and many (light tiles by single waves).  Bars: 1e-11 of the natural scale for the Hessian (its
+    cut truncates the third radial function at 2e-11 relative), 1e-12 for Phi, grad Phi and the multiscale field."""
+    v, t = star_surface(12, seed=8)
+    x = bbox_targets(v, n, pad=0.3, seed=n)
+    sig = 0.5 * triangle_diameters(v, t)
+    scale = 1.0 / (np.sqrt(2.0 * np.pi) * sig.min())
+    got = []
+    for far in (lss.FAR_DIRECT, lss.FAR_FMM):
+        c = lss.Context()
+        c.set_options(far_field=far)
+        c.set_sources(v, t, dunavant6())
+        c.set_sigma(sig)
+        got.append(c.eval_hessian(x) + c.eval_multiscale(x, 2.5, 0.1))
+    for k, (a, b, tol) in enumerate(zip(got[1], got[0], (1e-12, 1e-12 * scale, 1e-11 * scale / sig.min(),
+                                                         1e-12, 1e-12 * scale, 1e-12))):
+        assert np.abs(a - b).max() <= tol, k
