@@ -160,8 +160,8 @@ void build(Ctx &c) {
     c.pairs.ensure(sizeof(double) * 4);
     c.tile_queue.ensure(sizeof(unsigned int) * 4);
     LSS_HIP(hipMemsetAsync(c.tile_queue.p, 0, sizeof(unsigned int) * 4, c.stream));
-    c.tile_bucket.ensure(sizeof(int32_t) * (2 * kCostBuckets + 1));
-    LSS_HIP(hipMemsetAsync(c.tile_bucket.p, 0, sizeof(int32_t) * (2 * kCostBuckets + 1), c.stream));
+    c.tile_bucket.ensure(sizeof(int32_t) * (2 * kCostBuckets + 2));
+    LSS_HIP(hipMemsetAsync(c.tile_bucket.p, 0, sizeof(int32_t) * (2 * kCostBuckets + 2), c.stream));
     c.stats.n_boxes = c.stats.n_leaves = c.stats.n_m2l = c.stats.n_m2p = 0;
     c.stats.tree_depth = c.stats.fmm_order = 0;
     if (c.opt.far_field == LSS_FAR_FMM) build_fmm(c);

@@ -293,8 +293,8 @@ struct Ctx {
     DBuf part;                // partial sums of a direct evaluation whose nodes are split
     DBuf tile_queue;          // uint32[4] work queue of the FMM evaluation (zero between launches)
     DBuf tile_order;          // FMM tiles, most expensive first (int32 per tile)
-    DBuf tile_bucket;         // int32[2 * kCostBuckets + 1]: bucket counts (zero between uses), offsets,
-                              // heavy tiles
+    DBuf tile_bucket;         // int32[2 * kCostBuckets + 2]: bucket counts (zero between uses), offsets,
+                              // heavy tiles and their part of the cost
     bool pairs_pending = false;   // counter not yet read back into stats.last_pairs
     NewtonState ns;
 

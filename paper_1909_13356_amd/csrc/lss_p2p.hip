@@ -777,7 +777,9 @@ struct FmmEvalArgs {
     // workgroup to finish clears them)
     unsigned int *queue;
     const int32_t *order;       // queue position -> tile (most expensive first)
-    const int32_t *nheavy;      // tiles at the front of the order that a whole workgroup takes (for_tiles)
+    // tiles at the front of the order that a whole workgroup takes (for_tiles),
+    // and their part of the total cost in 1/1024
+    const int32_t *nheavy;
 };
 
 // next tile for the workgroup (uniform); tiles are handed out in list order
@@ -1314,11 +1316,10 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
 
 // ------------------------------------------------------- workgroups of waves
 // The FP64 evaluation kernels run persistent workgroups of up to kWide waves.
-// First the workgroups take the heavy tiles (k_tile_bucket_scan) one by one:
-// the waves share a tile's direct list chunk by chunk and its M2P boxes, each
-// with staging and totals of its own, and add the totals in wave order at the
-// end; there is no other barrier.  Then every wave takes light tiles by
-// itself.  One wave alone on a SIMD issues about every fifth cycle that it
+// A workgroup takes heavy tiles (k_tile_bucket_scan) one by one: the waves
+// share a tile's direct list chunk by chunk and its M2P boxes, each with
+// staging and totals of its own, and add the totals in wave order at the end;
+// there is no other barrier.  Light tiles go to single waves.  One wave alone on a SIMD issues about every fifth cycle that it
 // could (FP64 latency), so a tile of many times the usual cost, on one wave,
 // outlasts everything else: on 2e5 graded triangles a dozen of 40 000 tiles
 // hold 1e5 to 4e5 nodes and hundreds of M2P boxes where a usual one has 1e4.
@@ -1414,7 +1415,12 @@ __device__ __forceinline__ void wave_stage(const double *src, int ncp, double *b
 }
 
 // Tile loop of such a kernel: tile(t, W, w) for the heavy tiles with all the
-// W waves of a workgroup (w: this wave), then tile(t, 1, 0) wave by wave.
+// W waves of a workgroup (w: this wave), tile(t, 1, 0) wave by wave for the
+// light ones.  The share of the workgroups that the heavy tiles' cost calls for
+// starts with those, the others with the light tiles, which take a wave
+// longest; each goes on with the other kind.  (Heavy tiles first everywhere:
+// 2e5 targets on a uniform sphere, half of the tiles heavy, 7.8 ms against
+// 5.0, mixed.)
 // queue[2], queue[3]: next heavy tile, finished workgroups; queue[0]: next
 // light tile; cleared by the last workgroup.  A launch without tiles returns
 // at once (uniform over the grid).
@@ -1423,23 +1429,24 @@ __device__ __forceinline__ void for_tiles(const FmmEvalArgs &a, int *slot, F til
     const int ntiles = *a.ntiles_dev, heavy = min(*a.nheavy, ntiles);
     if (ntiles <= 0) return;
     const int waves = (int)(blockDim.x >> 6), self = (int)(threadIdx.x >> 6);
-    // one loop for both phases: two copies of the tile code would compete for
+    // one loop for both kinds: two copies of the tile code would compete for
     // the instruction cache while some workgroups are in either
-    for (bool together = heavy > 0;;) {
+    bool together = heavy > 0 && (int64_t)blockIdx.x * 1024 < (int64_t)a.nheavy[1] * gridDim.x;
+    for (int left = heavy > 0 ? 2 : 1;;) {
         int q = 0;
         if (together) {
             __syncthreads();                // everyone has read the slot and left the totals
             if (threadIdx.x == 0) *slot = (int)atomicAdd(a.queue + 2, 1u);
             __syncthreads();
             q = *slot;
-            if (q >= heavy) {
-                together = false;
-                continue;
-            }
         } else {
             if ((threadIdx.x & 63) == 0) q = (int)atomicAdd(a.queue, 1u);
             q = heavy + __builtin_amdgcn_readfirstlane(q);
-            if (q >= ntiles) break;
+        }
+        if (q >= (together ? heavy : ntiles)) {             // uniform: this kind is handed out
+            if (--left == 0) break;
+            together = !together;
+            continue;
         }
         tile(a.order[q], together ? waves : 1, together ? self : 0);
     }
@@ -1884,44 +1891,82 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
     });
 }
 
-// Mixed path: one wavefront per tile of 64 targets.  Each staged node is
-// tested against the tile's target bounding box: a node whose distance to the
-// box is beyond its cut radius (u >= KF32_X for every target of the tile)
-// goes to the far ring and the dipole-only loop, every other node to the near
-// ring and the general loop (float-float offsets, the rational fit for node
-// groups with a pair inside the cut).  Each ring is drained in runs of kRun
-// records, one compensated partial sum per run; the remainders are padded to
-// whole node groups at the end of the tile.  The rings share the dynamic LDS
-// with the local expansion, which is staged once the pairs are done.
+// Mixed path, in the tile loop of for_tiles.  Each staged node is tested
+// against the tile's target bounding box: a node whose distance to the box is
+// beyond its cut radius (u >= KF32_X for every target of the tile) goes to the
+// far ring and the dipole-only loop, every other node to the near ring and the
+// general loop (float-float offsets, the rational fit for node groups with a
+// pair inside the cut).  Each ring is drained in runs of kRun records, one
+// compensated partial sum per run; the remainders are padded to whole node
+// groups at the end of the tile.  The rings share the LDS with the expansions,
+// which are staged once the pairs are done.
+//   One wave (light tiles): stages 64 nodes at a time into rings of its own.
+//   A workgroup (heavy tiles): the same results bit for bit, whichever way a
+// tile is taken.  The waves stage kWide chunks of 64 nodes at a time into
+// shared rings in list order, so a run holds the same nodes; each run is
+// summed by one wave, and wave 0 folds the runs' sums in the order in which one
+// wave would have completed them (chunk by chunk, near runs before far ones).
+// The expansions go to the waves in turn and are added in list order.
+// Bound by FP32 VALU issue at four waves per SIMD.  One wave per tile before:
+// 1000 targets on 242 000 nodes 3.4 -> 0.75 ms; a graded surface of 31 212
+// triangles with 1e4 to 2e5 targets 18.8 -> 3.5 ms, 8e5 targets 20.5 -> 6.5 ms;
+// 5e7 targets on 2e6 triangles as before.
 constexpr int kRun = 32;                 // records per partial sum
-
-constexpr int kRing = 96;                // ring capacity: kRun - 1 left over + 64 staged
+constexpr int kRing = 96;                // a wave's ring: kRun - 1 left over + 64 staged
+constexpr int kRingW = 64 * kWide + 32;  // a workgroup's: kRun - 1 left over + kWide * 64 staged
+constexpr int kRunsW = (64 * kWide + 62) / kRun + 1;    // runs of both rings completed at once
+static_assert(kRing % kRun == 0 && kRingW % kRun == 0, "a run is contiguous in its ring");
 constexpr size_t kMixedRingBytes = kRing * (sizeof(SrcF) + sizeof(FarF));
+constexpr size_t kMixedWideBytes = kRingW * (sizeof(SrcF) + sizeof(FarF)) + kRunsW * 4 * 64 * sizeof(float);
+
+// record of a node at offset (qx, qy, qz) from the tile origin, near and far
+__device__ __forceinline__ SrcF mixed_near(const Src &sr, double qx, double qy, double qz) {
+    SrcF f;
+    f.yx = (float)qx;
+    f.yy = (float)qy;
+    f.yz = (float)qz;
+    f.lx = (float)(qx - (double)f.yx);
+    f.ly = (float)(qy - (double)f.yy);
+    f.lz = (float)(qz - (double)f.yz);
+    f.s2 = (float)sr.s2;
+    f.ax = (float)(kFoldA * sr.ax);
+    f.ay = (float)(kFoldA * sr.ay);
+    f.az = (float)(kFoldA * sr.az);
+    f.s2x2 = (float)(kFoldT * sr.s2x2);
+    f.pad = 0.0f;
+    return f;
+}
+__device__ __forceinline__ FarF mixed_far(const Src &sr, double qx, double qy, double qz) {
+    const double fa = kFoldA / (sr.s2 * sqrt(sr.s2));     // a'' (nodes32_far)
+    FarF f;
+    f.yx = (float)qx;
+    f.yy = (float)qy;
+    f.yz = (float)qz;
+    f.ax = (float)(fa * sr.ax);
+    f.ay = (float)(fa * sr.ay);
+    f.az = (float)(fa * sr.az);
+    f.pad0 = f.pad1 = 0.0f;
+    return f;
+}
 
 template <bool COUNT>
-__global__ __launch_bounds__(64) void k_eval_fmm_mixed(FmmEvalArgs a) {
-    constexpr int W = 64;
-    __shared__ RangeBatch<W> rb;
-    __shared__ double tbox[6];          // the tile's target bounding box (offsets from its origin)
-    // node rings while the pairs run, then the local expansion (ncp doubles)
-    // and the M2P staging buffer
+__global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_fmm_mixed_waves(FmmEvalArgs a,
+                                                                                                        int region_doubles,
+                                                                                                        int nexp) {
+    __shared__ WaveLds wl[kWide];
+    __shared__ int cnts[2][2][kWide], slot;         // heavy tiles: near and far nodes per chunk, of this step and the last
+    __shared__ double scale[kWide];                 // and 1 / side of the boxes of the expansions
     extern __shared__ __attribute__((aligned(16))) double Ls[];
-    SrcF *ring_n = reinterpret_cast<SrcF *>(Ls);
-    FarF *ring_f = reinterpret_cast<FarF *>(ring_n + kRing);
+    const int lane = threadIdx.x & 63, self = threadIdx.x >> 6;
     const int ntiles = *a.ntiles_dev;
     const int64_t n = a.n_dev ? (int64_t)*a.n_dev : a.n_max;
-    const int lane = threadIdx.x;
     const double far_u = (double)KF32_X * (1.0 + 1e-4);     // margin over the FP32 rounding of u
-    __shared__ int slot;
-    // uniform over the grid: the queue is not touched (a launch without targets,
-    // as the last iterations of a captured projection are, took 430 us)
-    if (ntiles <= 0) return;
-    for (int q = next_tile(a, &slot); q < ntiles; q = next_tile(a, &slot)) {
-        const int tile = a.order[q];
+    for_tiles(a, &slot, [&](int tile, int W, int w) {
         const int64_t s0 = a.tile_start[tile];
         const int32_t B = a.sleaf[s0];
-        if (B >= a.nboxes) continue;        // outside the root cube: k_eval_outside
+        if (B >= a.nboxes) return;          // outside the root cube: k_eval_outside
         const int64_t s1 = tile + 1 < ntiles ? (int64_t)a.tile_start[tile + 1] : n;   // tile = [s0, s1)
+        const int nt = (int)(s1 - s0);
         const int64_t sp_ = s0 + lane;
         const bool valid = sp_ < s1;
         const int64_t ti = a.sidx ? (int64_t)a.sidx[valid ? sp_ : s0] : (valid ? sp_ : s0);
@@ -1931,96 +1976,95 @@ __global__ __launch_bounds__(64) void k_eval_fmm_mixed(FmmEvalArgs a) {
         const float x = (float)dxo, y = (float)dyo, z = (float)dzo;
         const float xl = (float)(dxo - (double)x), yl = (float)(dyo - (double)y), zl = (float)(dzo - (double)z);
         const int e0 = a.p2p_beg[B], e1 = a.p2p_end[B];
-        // bounding box of the tile's targets (offsets from the origin; the
-        // lanes past the tile end hold the first target)
-        double blo[3] = {dxo, dyo, dzo}, bhi[3] = {dxo, dyo, dzo};
-        for (int off = 32; off > 0; off >>= 1)
-            for (int c = 0; c < 3; ++c) {
-                blo[c] = fmin(blo[c], __shfl_xor(blo[c], off));
-                bhi[c] = fmax(bhi[c], __shfl_xor(bhi[c], off));
-            }
-        __syncthreads();                    // the previous tile is done with tbox
-        if (lane == 0)
-            for (int c = 0; c < 3; ++c) {
-                tbox[c] = blo[c];
-                tbox[3 + c] = bhi[c];
-            }
-        float sp = 0, ep = 0, sx = 0, ex = 0, sy = 0, ey = 0, sz = 0, ez = 0;
-        double npair = 0.0, nfar = 0.0;
-        uint32_t nuse = 0;
-        int hn = 0, nn = 0, hf = 0, nf = 0;     // head and fill of each ring (uniform)
-        for (int eb = e0; eb < e1; eb += W) {
-            const int nr = e1 - eb < W ? e1 - eb : W;
-            __syncthreads();
-            const int64_t total = load_ranges<W>(a, rb, eb, nr);
-            npair += (double)total;
-            for (int64_t c0 = 0; c0 < total; c0 += W) {
-                const int cnt = (int)(total - c0 < W ? total - c0 : W);
-                Src sr;
-                double qx = 0.0, qy = 0.0, qz = 0.0;
-                bool isfar = false;
-                if (lane < cnt) {
-                    sr = a.src[packed_node<W>(rb, nr, c0 + lane)];
-                    qx = sr.yx - ox;
-                    qy = sr.yy - oy;
-                    qz = sr.yz - oz;
-                    const double gx_ = fmax(fmax(tbox[0] - qx, qx - tbox[3]), 0.0);
-                    const double gy_ = fmax(fmax(tbox[1] - qy, qy - tbox[4]), 0.0);
-                    const double gz_ = fmax(fmax(tbox[2] - qz, qz - tbox[5]), 0.0);
-                    isfar = (gx_ * gx_ + gy_ * gy_ + gz_ * gz_) * sr.s2 >= far_u;
-                }
-                const uint64_t fm = __ballot(isfar), nm = __ballot(lane < cnt && !isfar);
-                __syncthreads();                // the runs taken last are read
-                if (lane < cnt && !isfar) {
-                    int pos = hn + nn + below(nm);
-                    if (pos >= kRing) pos -= kRing;
-                    SrcF f;
-                    f.yx = (float)qx;
-                    f.yy = (float)qy;
-                    f.yz = (float)qz;
-                    f.lx = (float)(qx - (double)f.yx);
-                    f.ly = (float)(qy - (double)f.yy);
-                    f.lz = (float)(qz - (double)f.yz);
-                    f.s2 = (float)sr.s2;
-                    f.ax = (float)(kFoldA * sr.ax);
-                    f.ay = (float)(kFoldA * sr.ay);
-                    f.az = (float)(kFoldA * sr.az);
-                    f.s2x2 = (float)(kFoldT * sr.s2x2);
-                    f.pad = 0.0f;
-                    ring_n[pos] = f;
-                } else if (isfar) {
-                    int pos = hf + nf + below(fm);
-                    if (pos >= kRing) pos -= kRing;
-                    const double fa = kFoldA / (sr.s2 * sqrt(sr.s2));     // a'' (nodes32_far)
-                    FarF f;
-                    f.yx = (float)qx;
-                    f.yy = (float)qy;
-                    f.yz = (float)qz;
-                    f.ax = (float)(fa * sr.ax);
-                    f.ay = (float)(fa * sr.ay);
-                    f.az = (float)(fa * sr.az);
-                    f.pad0 = f.pad1 = 0.0f;
-                    ring_f[pos] = f;
-                }
-                nn += __popcll(nm);
-                nf += __popcll(fm);
-                if (COUNT) nfar += (double)__popcll(fm);
-                __syncthreads();
-                for (; nn >= kRun; nn -= kRun) {
-                    float p = 0, gx = 0, gy = 0, gz = 0;
+        // bounding box of the tile's targets (offsets from the origin), one
+        // copy per wave; heavy tiles share wave 0's range list
+        double *box = wl[self].box;
+        wave_box(dxo, dyo, dzo, box);
+        RangeList &rl = wl[W > 1 ? 0 : self].rl;
+        SrcF *ring_n = reinterpret_cast<SrcF *>(W > 1 ? Ls : Ls + region_doubles * self);
+        FarF *ring_f = reinterpret_cast<FarF *>(ring_n + (W > 1 ? kRingW : kRing));
+        if (W == 1) {
+            float sp = 0, ep = 0, sx = 0, ex = 0, sy = 0, ey = 0, sz = 0, ez = 0;
+            double npair = 0.0, nfar = 0.0;
+            uint32_t nuse = 0;
+            int hn = 0, nn = 0, hf = 0, nf = 0;     // head and fill of each ring (uniform)
+            for (int eb = e0; eb < e1; eb += 64) {
+                const int nr = e1 - eb < 64 ? e1 - eb : 64;
+                const int total = wave_ranges(a, rl, eb, nr);
+                npair += (double)total;
+                for (int c0 = 0; c0 < total; c0 += 64) {
+                    const int cnt = total - c0 < 64 ? total - c0 : 64;
+                    Src sr;
+                    double qx = 0.0, qy = 0.0, qz = 0.0;
+                    bool isfar = false;
+                    if (lane < cnt) {
+                        sr = a.src[range_node(rl, nr, c0 + lane)];
+                        qx = sr.yx - ox;
+                        qy = sr.yy - oy;
+                        qz = sr.yz - oz;
+                        isfar = box_gap2(box, qx, qy, qz) * sr.s2 >= far_u;
+                    }
+                    const uint64_t fm = __ballot(isfar), nm = __ballot(lane < cnt && !isfar);
+                    wave_sync();                // the runs taken last are read
+                    if (lane < cnt && !isfar) {
+                        int pos = hn + nn + below(nm);
+                        if (pos >= kRing) pos -= kRing;
+                        ring_n[pos] = mixed_near(sr, qx, qy, qz);
+                    } else if (isfar) {
+                        int pos = hf + nf + below(fm);
+                        if (pos >= kRing) pos -= kRing;
+                        ring_f[pos] = mixed_far(sr, qx, qy, qz);
+                    }
+                    nn += __popcll(nm);
+                    nf += __popcll(fm);
+                    if (COUNT) nfar += (double)__popcll(fm);
+                    wave_sync();
+                    for (; nn >= kRun; nn -= kRun) {
+                        float p = 0, gx = 0, gy = 0, gz = 0;
 #pragma unroll 1
-                    for (int j = 0; j < kRun; j += kNodeGroup)
+                        for (int j = 0; j < kRun; j += kNodeGroup)
+                            nodes32<kNodeGroup, COUNT>(ring_n + hn + j, x, y, z, xl, yl, zl, p, gx, gy, gz, &nuse);
+                        two_sum_f(sp, ep, p);
+                        two_sum_f(sx, ex, gx);
+                        two_sum_f(sy, ey, gy);
+                        two_sum_f(sz, ez, gz);
+                        hn = hn + kRun == kRing ? 0 : hn + kRun;
+                    }
+                    for (; nf >= kRun; nf -= kRun) {
+                        float p = 0, gx = 0, gy = 0, gz = 0, hx = 0, hy = 0, hz = 0;
+#pragma unroll 1
+                        for (int j = 0; j < kRun; j += kNodeGroup)
+                            nodes32_far<kNodeGroup>(ring_f + hf + j, x, y, z, p, gx, gy, gz, hx, hy, hz);
+                        gx = fmaf(3.0f, gx, -hx);
+                        gy = fmaf(3.0f, gy, -hy);
+                        gz = fmaf(3.0f, gz, -hz);
+                        two_sum_f(sp, ep, p);
+                        two_sum_f(sx, ex, gx);
+                        two_sum_f(sy, ey, gy);
+                        two_sum_f(sz, ez, gz);
+                        hf = hf + kRun == kRing ? 0 : hf + kRun;
+                    }
+                }
+            }
+            if (nn > 0 || nf > 0) {             // remainders (< kRun each), padded to whole node groups
+                const int pn = (nn + kNodeGroup - 1) / kNodeGroup * kNodeGroup;
+                const int pf = (nf + kNodeGroup - 1) / kNodeGroup * kNodeGroup;
+                wave_sync();
+                if (lane >= nn && lane < pn) ring_n[hn + lane] = pad_srcf();    // hn + kRun <= kRing
+                if (lane >= nf && lane < pf) ring_f[hf + lane] = pad_farf();
+                wave_sync();
+                if (nn > 0) {
+                    float p = 0, gx = 0, gy = 0, gz = 0;
+                    for (int j = 0; j < pn; j += kNodeGroup)
                         nodes32<kNodeGroup, COUNT>(ring_n + hn + j, x, y, z, xl, yl, zl, p, gx, gy, gz, &nuse);
                     two_sum_f(sp, ep, p);
                     two_sum_f(sx, ex, gx);
                     two_sum_f(sy, ey, gy);
                     two_sum_f(sz, ez, gz);
-                    hn = hn + kRun == kRing ? 0 : hn + kRun;
                 }
-                for (; nf >= kRun; nf -= kRun) {
+                if (nf > 0) {
                     float p = 0, gx = 0, gy = 0, gz = 0, hx = 0, hy = 0, hz = 0;
-#pragma unroll 1
-                    for (int j = 0; j < kRun; j += kNodeGroup)
+                    for (int j = 0; j < pf; j += kNodeGroup)
                         nodes32_far<kNodeGroup>(ring_f + hf + j, x, y, z, p, gx, gy, gz, hx, hy, hz);
                     gx = fmaf(3.0f, gx, -hx);
                     gy = fmaf(3.0f, gy, -hy);
@@ -2029,77 +2073,228 @@ __global__ __launch_bounds__(64) void k_eval_fmm_mixed(FmmEvalArgs a) {
                     two_sum_f(sx, ex, gx);
                     two_sum_f(sy, ey, gy);
                     two_sum_f(sz, ez, gz);
-                    hf = hf + kRun == kRing ? 0 : hf + kRun;
                 }
+            }
+            const double X = a.tx[ti], Y = a.ty[ti], Z = a.tz[ti];
+            double ph = 0.0, g[3] = {0.0, 0.0, 0.0}, mph = 0.0, mg[3] = {0.0, 0.0, 0.0};
+            double *buf = reinterpret_cast<double *>(ring_n);       // the rings are done with
+            for (int e = a.m2p_beg[B]; e < a.m2p_end[B]; ++e) {
+                const int32_t S = a.m2p_src[e];
+                wave_stage(a.M + (int64_t)S * a.ncp, a.ncp, buf);
+                double r[3], inv, p1, g1[3];
+                box_position(a, S, X, Y, Z, r, inv);
+                fmm::m2p(buf, r[0], r[1], r[2], inv, a.p, p1, g1);
+                mph += p1;
+                for (int c = 0; c < 3; ++c) mg[c] += g1[c];
+            }
+            wave_stage(a.L + (int64_t)B * a.ncp, a.ncp, buf);
+            fmm_l2p(a, B, buf, X, Y, Z, ph, g);
+            ph += mph;
+            g[0] += mg[0];
+            g[1] += mg[1];
+            g[2] += mg[2];
+            if (valid) {
+                const int64_t o = a.out_idx ? (int64_t)a.out_idx[ti] : ti;
+                a.phi[o] = ((double)sp + (double)ep) + ph;
+                if (a.grad) {
+                    a.grad[3 * o] = ((double)sx + (double)ex) + g[0];
+                    a.grad[3 * o + 1] = ((double)sy + (double)ey) + g[1];
+                    a.grad[3 * o + 2] = ((double)sz + (double)ez) + g[2];
+                }
+            }
+            if (a.pairs) {                      // [0] pairs of real targets, [1] lane slots spent, [2] inside the cut,
+                                                // [3] taken by the dipole-only loop
+                const double wu = COUNT ? wave_sum(valid ? (double)nuse : 0.0) : 0.0;
+                if (lane == 0) {
+                    atomicAdd(a.pairs, (double)nt * npair);
+                    atomicAdd(a.pairs + 1, 64.0 * npair);
+                    if (COUNT) {
+                        atomicAdd(a.pairs + 2, wu);
+                        atomicAdd(a.pairs + 3, (double)nt * nfar);
+                    }
+                }
+            }
+            return;
+        }
+        float *part = reinterpret_cast<float *>(ring_f + kRingW);       // [run][component][lane]
+        float sp = 0, ep = 0, sx = 0, ex = 0, sy = 0, ey = 0, sz = 0, ez = 0;      // wave 0's totals
+        double npair = 0.0, nfar = 0.0;
+        uint32_t nuse = 0;
+        int hn = 0, nn = 0, hf = 0, nf = 0;     // head and fill of each ring (uniform)
+        int par = 0;
+        // sums of a run of a ring into slot u
+        auto run = [&](bool near, int at, int len, int u) {
+            float p = 0, gx = 0, gy = 0, gz = 0;
+            if (near) {
+#pragma unroll 1
+                for (int j = 0; j < len; j += kNodeGroup)
+                    nodes32<kNodeGroup, COUNT>(ring_n + at + j, x, y, z, xl, yl, zl, p, gx, gy, gz, &nuse);
+            } else {
+                float hx = 0, hy = 0, hz = 0;
+#pragma unroll 1
+                for (int j = 0; j < len; j += kNodeGroup)
+                    nodes32_far<kNodeGroup>(ring_f + at + j, x, y, z, p, gx, gy, gz, hx, hy, hz);
+                gx = fmaf(3.0f, gx, -hx);
+                gy = fmaf(3.0f, gy, -hy);
+                gz = fmaf(3.0f, gz, -hz);
+            }
+            float *o = part + u * 256 + lane;
+            o[0] = p;
+            o[64] = gx;
+            o[128] = gy;
+            o[192] = gz;
+        };
+        auto fold = [&](int u) {
+            const float *o = part + u * 256 + lane;
+            two_sum_f(sp, ep, o[0]);
+            two_sum_f(sx, ex, o[64]);
+            two_sum_f(sy, ey, o[128]);
+            two_sum_f(sz, ez, o[192]);
+        };
+        for (int eb = e0; eb < e1; eb += 64) {
+            const int nr = e1 - eb < 64 ? e1 - eb : 64;
+            __syncthreads();                // the previous batch is done with
+            if (w == 0) wave_ranges(a, rl, eb, nr);
+            __syncthreads();
+            const int total = rl.off[nr];
+            npair += (double)total;
+            for (int c0 = 0; c0 < total; c0 += 64 * kWide) {
+                const int c1 = c0 + 64 * w, cnt = min(max(total - c1, 0), 64);
+                Src sr;
+                double qx = 0.0, qy = 0.0, qz = 0.0;
+                bool isfar = false;
+                if (lane < cnt) {
+                    sr = a.src[range_node(rl, nr, c1 + lane)];
+                    qx = sr.yx - ox;
+                    qy = sr.yy - oy;
+                    qz = sr.yz - oz;
+                    isfar = box_gap2(box, qx, qy, qz) * sr.s2 >= far_u;
+                }
+                const uint64_t fm = __ballot(isfar), nm = __ballot(lane < cnt && !isfar);
+                par ^= 1;                   // wave 0 may still fold with the last step's counts
+                int *cntn = cnts[par][0], *cntf = cnts[par][1];
+                if (lane == 0) {
+                    cntn[w] = __popcll(nm);
+                    cntf[w] = __popcll(fm);
+                }
+                __syncthreads();            // counts; the runs taken last are read and folded
+                int bn = nn, bf = nf, tn = nn, tf = nf;
+                for (int v = 0; v < kWide; ++v) {
+                    if (v < w) {
+                        bn += cntn[v];
+                        bf += cntf[v];
+                    }
+                    tn += cntn[v];
+                    tf += cntf[v];
+                }
+                if (lane < cnt && !isfar) {
+                    int pos = hn + bn + below(nm);
+                    if (pos >= kRingW) pos -= kRingW;
+                    ring_n[pos] = mixed_near(sr, qx, qy, qz);
+                } else if (isfar) {
+                    int pos = hf + bf + below(fm);
+                    if (pos >= kRingW) pos -= kRingW;
+                    ring_f[pos] = mixed_far(sr, qx, qy, qz);
+                }
+                if (COUNT) nfar += (double)(tf - nf);
+                __syncthreads();
+                const int rn = tn / kRun, rf = tf / kRun;
+                for (int u = w; u < rn + rf; u += kWide) {
+                    int at = u < rn ? hn + u * kRun : hf + (u - rn) * kRun;
+                    if (at >= kRingW) at -= kRingW;
+                    run(u < rn, at, kRun, u);
+                }
+                __syncthreads();
+                if (w == 0) {               // fold chunk by chunk
+                    int kn = nn, kf = nf, dn = 0, df = 0;
+                    for (int v = 0; v < kWide; ++v) {
+                        kn += cntn[v];
+                        kf += cntf[v];
+                        for (; dn < kn / kRun; ++dn) fold(dn);
+                        for (; df < kf / kRun; ++df) fold(rn + df);
+                    }
+                }
+                hn += rn * kRun;
+                if (hn >= kRingW) hn -= kRingW;
+                hf += rf * kRun;
+                if (hf >= kRingW) hf -= kRingW;
+                nn = tn - rn * kRun;
+                nf = tf - rf * kRun;
             }
         }
         if (nn > 0 || nf > 0) {             // remainders (< kRun each), padded to whole node groups
             const int pn = (nn + kNodeGroup - 1) / kNodeGroup * kNodeGroup;
             const int pf = (nf + kNodeGroup - 1) / kNodeGroup * kNodeGroup;
             __syncthreads();
-            if (lane >= nn && lane < pn) ring_n[hn + lane] = pad_srcf();    // hn + kRun <= kRing
-            if (lane >= nf && lane < pf) ring_f[hf + lane] = pad_farf();
+            if (w == 0 && lane >= nn && lane < pn) ring_n[hn + lane] = pad_srcf();
+            if (w == 1 && lane >= nf && lane < pf) ring_f[hf + lane] = pad_farf();
             __syncthreads();
-            if (nn > 0) {
-                float p = 0, gx = 0, gy = 0, gz = 0;
-                for (int j = 0; j < pn; j += kNodeGroup)
-                    nodes32<kNodeGroup, COUNT>(ring_n + hn + j, x, y, z, xl, yl, zl, p, gx, gy, gz, &nuse);
-                two_sum_f(sp, ep, p);
-                two_sum_f(sx, ex, gx);
-                two_sum_f(sy, ey, gy);
-                two_sum_f(sz, ez, gz);
-            }
-            if (nf > 0) {
-                float p = 0, gx = 0, gy = 0, gz = 0, hx = 0, hy = 0, hz = 0;
-                for (int j = 0; j < pf; j += kNodeGroup)
-                    nodes32_far<kNodeGroup>(ring_f + hf + j, x, y, z, p, gx, gy, gz, hx, hy, hz);
-                gx = fmaf(3.0f, gx, -hx);
-                gy = fmaf(3.0f, gy, -hy);
-                gz = fmaf(3.0f, gz, -hz);
-                two_sum_f(sp, ep, p);
-                two_sum_f(sx, ex, gx);
-                two_sum_f(sy, ey, gy);
-                two_sum_f(sz, ez, gz);
+            if (w == 0 && nn > 0) run(true, hn, pn, 0);
+            if (w == 1 && nf > 0) run(false, hf, pf, 1);
+            __syncthreads();
+            if (w == 0) {
+                if (nn > 0) fold(0);
+                if (nf > 0) fold(1);
             }
         }
+        // expansions: entry 0 the leaf's local one, then the M2P list, nexp at a
+        // time, one per wave; wave 0 scales and adds them in list order, each
+        // product and sum in one rounding as where one wave takes the tile (the
+        // compiler contracts them there)
         const double X = a.tx[ti], Y = a.ty[ti], Z = a.tz[ti];
-        double ph = 0.0, g[3] = {0.0, 0.0, 0.0}, mph = 0.0, mg[3] = {0.0, 0.0, 0.0};
-        if (a.m2p_end[B] > a.m2p_beg[B])    // uniform: Ls is the M2P staging buffer first
-            fmm_m2p_list(a, B, Ls, X, Y, Z, mph, mg);
-        __syncthreads();                    // the rings (or the M2P buffer) are done
-        stage_local(a, B, Ls);
-        __syncthreads();                    // Ls staged
-        fmm_l2p(a, B, Ls, X, Y, Z, ph, g);
-        ph += mph;
-        g[0] += mg[0];
-        g[1] += mg[1];
-        g[2] += mg[2];
-        if (valid) {
-            const int64_t o = a.out_idx ? (int64_t)a.out_idx[ti] : ti;
-            a.phi[o] = ((double)sp + (double)ep) + ph;
-            if (a.grad) {
-                a.grad[3 * o] = ((double)sx + (double)ex) + g[0];
-                a.grad[3 * o + 1] = ((double)sy + (double)ey) + g[1];
-                a.grad[3 * o + 2] = ((double)sz + (double)ez) + g[2];
+        double *res = Ls, *buf = Ls + nexp * 256 + w * a.ncp;      // [wave][sum][lane], then the buffers
+        double lv[4] = {0.0, 0.0, 0.0, 0.0}, mv[4] = {0.0, 0.0, 0.0, 0.0}, linv = 0.0;
+        const int m0 = a.m2p_beg[B], entries = 1 + a.m2p_end[B] - m0;
+        for (int k0 = 0; k0 < entries; k0 += nexp) {
+            const int k = k0 + w;
+            __syncthreads();                // the rings, or the results folded last, are done with
+            if (w < nexp && k < entries) {
+                const int32_t S = k == 0 ? B : a.m2p_src[m0 + k - 1];
+                wave_stage((k == 0 ? a.L : a.M) + (int64_t)S * a.ncp, a.ncp, buf);
+                double r[3], inv, sums[4];
+                box_position(a, S, X, Y, Z, r, inv);
+                if (k == 0) fmm::l2p_sums(buf, r[0], r[1], r[2], a.p, sums);
+                else fmm::m2p_sums(buf, r[0], r[1], r[2], a.p, sums);
+                for (int c = 0; c < 4; ++c) res[w * 256 + 64 * c + lane] = sums[c];
+                if (lane == 0) scale[w] = inv;
             }
-        }
-        if (a.pairs) {                      // [0] pairs of real targets, [1] lane slots spent, [2] inside the cut,
-                                            // [3] taken by the dipole-only loop
-            const double w = wave_sum(valid ? npair : 0.0), wl = wave_sum(npair);
-            const double wu = COUNT ? wave_sum(valid ? (double)nuse : 0.0) : 0.0;
-            const double wf = COUNT ? wave_sum(valid ? nfar : 0.0) : 0.0;
-            if (lane == 0) {
-                atomicAdd(a.pairs, w);
-                atomicAdd(a.pairs + 1, wl);
-                if (COUNT) {
-                    atomicAdd(a.pairs + 2, wu);
-                    atomicAdd(a.pairs + 3, wf);
+            __syncthreads();
+            if (w == 0)
+                for (int v = 0; v < nexp && k0 + v < entries; ++v) {
+                    const double *e = res + v * 256 + lane;
+                    const double inv = scale[v], is2 = inv * inv;
+                    if (k0 + v == 0) {
+                        for (int c = 0; c < 4; ++c) lv[c] = e[64 * c];
+                        linv = inv;
+                    } else {
+                        mv[0] = fma(e[0], inv, mv[0]);
+                        mv[1] = fma(-e[64], is2, mv[1]);
+                        mv[2] = fma(e[128], is2, mv[2]);
+                        mv[3] = fma(-e[192], is2, mv[3]);
+                    }
                 }
+        }
+        if (w == 0 && valid) {
+            const int64_t o = a.out_idx ? (int64_t)a.out_idx[ti] : ti;
+            a.phi[o] = ((double)sp + (double)ep) + (lv[0] + mv[0]);
+            if (a.grad) {
+                a.grad[3 * o] = ((double)sx + (double)ex) + fma(lv[1], linv, mv[1]);
+                a.grad[3 * o + 1] = ((double)sy + (double)ey) + fma(lv[2], linv, mv[2]);
+                a.grad[3 * o + 2] = ((double)sz + (double)ez) + fma(lv[3], linv, mv[3]);
             }
         }
-        __syncthreads();                    // Ls is read before the next tile's rings overwrite it
-    }
-    queue_done(a);
+        if (a.pairs) {                      // as k_eval_fmm_mixed; the list counts once per tile
+            const double wu = COUNT ? wave_sum(valid ? (double)nuse : 0.0) : 0.0;
+            if (lane == 0) {
+                if (w == 0) {
+                    atomicAdd(a.pairs, (double)nt * npair);
+                    atomicAdd(a.pairs + 1, 64.0 * npair);
+                    if (COUNT) atomicAdd(a.pairs + 3, (double)nt * nfar);
+                }
+                if (COUNT) atomicAdd(a.pairs + 2, wu);
+            }
+        }
+    });
 }
 
 // targets per workgroup of the direct sum
@@ -2139,6 +2334,17 @@ void launch_hess_tile(Ctx &c, unsigned grid, const FmmEvalArgs &a, double *hess)
     const size_t shm = sizeof(double) * (size_t)a.ncp;
     hipLaunchKernelGGL(k_hess_fmm<TILE>, dim3(grid), dim3(TILE), shm, c.stream, a, hess);
     LSS_CHECK_LAUNCH("k_hess_fmm");
+}
+
+// nexp: expansions of a heavy tile evaluated at once (their buffers and
+// results fit the rings' LDS)
+void launch_mixed_waves(Ctx &c, int64_t max_tiles, const FmmEvalArgs &a) {
+    const size_t region = region_for(std::max(kMixedRingBytes, (kMixedWideBytes + kWide - 1) / kWide), a.ncp);
+    const int nexp = (int)std::min<size_t>(kWide, region * kWide / (sizeof(double) * (256 + (size_t)a.ncp)));
+    const unsigned grid = (unsigned)std::min<int64_t>(max_tiles > 0 ? max_tiles : 1, kWideWaves / kWide);
+    auto k = c.opt.count_useful ? k_eval_fmm_mixed_waves<true> : k_eval_fmm_mixed_waves<false>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * kWide), region * kWide, c.stream, a, (int)(region / sizeof(double)), nexp);
+    LSS_CHECK_LAUNCH("k_eval_fmm_mixed_waves");
 }
 
 // persistent workgroups of waves: two of kWide waves fill a CU at 128 VGPRs
@@ -2260,12 +2466,7 @@ void launch_eval_fmm(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const
         return;
     }
     if (c.opt.precision == LSS_MIXED) {
-        const size_t shm = std::max(kMixedRingBytes, sizeof(double) * (size_t)a.ncp);
-        if (c.opt.count_useful)
-            hipLaunchKernelGGL(k_eval_fmm_mixed<true>, dim3(grid), dim3(64), shm, c.stream, a);
-        else
-            hipLaunchKernelGGL(k_eval_fmm_mixed<false>, dim3(grid), dim3(64), shm, c.stream, a);
-        LSS_CHECK_LAUNCH("k_eval_fmm_mixed");
+        launch_mixed_waves(c, max_tiles, a);
     } else {
         switch (fmm_tile(c)) {
             case 64: launch_f64_waves(c, max_tiles, a); break;

@@ -593,13 +593,17 @@ __global__ void k_tile_bucket_count(int64_t max_tiles, const int32_t *__restrict
 // single block: offsets from the counts, counts cleared for the next use, and
 // how many of the first (most expensive) tiles are heavy: a whole workgroup
 // takes each of them (for_tiles in lss_p2p.hip).  The line: a cost of at least
-// 1 / kHeavyShare of what each of the chip's resident waves gets, so that the
-// tiles that single waves take end within an eighth of the launch of each
-// other.  At 1/4, 4.7e5 chart nodes left little more than one round of light
-// tiles, each a quarter of the launch long: 16.0 ms an evaluation against 12.6
-// at 1/8 and 13.0 at 1/2; 2e6 targets (40 000 tiles): 70 ms with any.
-constexpr double kHeavyShare = 8.0;
-__global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket) {
+// 1 / share of what each of the chip's resident waves gets, so that the tiles
+// that single waves take end within that part of the launch of each other.
+//   FP64, 8: the waves of a heavy tile are independent, nothing is lost on it.
+// 4e5 targets near a uniform sphere, and on a graded surface (ms): 22.6, 11.8
+// at 8; 22.6, 13.5 at 4; 31.7, 13.8 at 2 (one wave per tile: 25.5, 48.0).
+//   Mixed, 1.4: a heavy tile's waves work in step, 15% slower than single
+// waves where the chip is full anyway.  3e5 targets near the sphere, 8e5 on the
+// graded surface (ms): 6.9, 6.9 at 1.4; 6.7, 7.1 at 1; 7.9, 6.5 at 2 (one wave
+// per tile: 7.4, 21.2).
+constexpr double kHeavyShare64 = 8.0, kHeavyShareMixed = 1.4;
+__global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket, double share) {
     constexpr int kPer = kCostBuckets / 64;
     const int lane = threadIdx.x;
     int32_t n[kPer], s = 0;
@@ -619,14 +623,26 @@ __global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket) {
     }
     at -= s;                                            // tiles of the lanes below
     int32_t heavy = 0;
+    double hc = 0.0;
     for (int k = 0; k < kPer; ++k) {
         const int i = kPer * lane + k;
         bucket[kCostBuckets + i] = at;
         at += n[k];
-        if (bucket_cost(i) * kWideWaves * kHeavyShare >= total) heavy = at;
+        if (bucket_cost(i) * kWideWaves * share >= total) {
+            heavy = at;
+            hc += n[k] * bucket_cost(i);
+        }
     }
-    for (int d = 32; d > 0; d >>= 1) heavy = max(heavy, __shfl_xor(heavy, d));
-    if (lane == 0) bucket[2 * kCostBuckets] = heavy;
+    for (int d = 32; d > 0; d >>= 1) {
+        heavy = max(heavy, __shfl_xor(heavy, d));
+        hc += __shfl_xor(hc, d);
+    }
+    if (lane == 0) {
+        bucket[2 * kCostBuckets] = heavy;
+        // their cost's part, but a sixteenth of the workgroups for the first of
+        // them at least: the longest tile bounds the launch
+        bucket[2 * kCostBuckets + 1] = total > 0.0 ? max((int32_t)ceil(1024.0 * hc / total), min(2 * heavy, 64)) : 0;
+    }
 }
 
 __global__ void k_tile_bucket_scatter(int64_t max_tiles, const int32_t *__restrict__ ntiles_dev,
@@ -1028,7 +1044,8 @@ void order_tiles(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const int
     const unsigned g = grid_for(max_tiles) < 2048u ? grid_for(max_tiles) : 2048u;
     hipLaunchKernelGGL(k_tile_bucket_count, dim3(g), dim3(kBlk), 0, c.stream, max_tiles, ntiles_dev, tile_start, leaf,
                        t.near_cnt.as<int64_t>(), c.tile_bucket.as<int32_t>());
-    hipLaunchKernelGGL(k_tile_bucket_scan, dim3(1), dim3(64), 0, c.stream, c.tile_bucket.as<int32_t>());
+    hipLaunchKernelGGL(k_tile_bucket_scan, dim3(1), dim3(64), 0, c.stream, c.tile_bucket.as<int32_t>(),
+                       c.opt.precision == LSS_MIXED ? kHeavyShareMixed : kHeavyShare64);
     hipLaunchKernelGGL(k_tile_bucket_scatter, dim3(g), dim3(kBlk), 0, c.stream, max_tiles, ntiles_dev, tile_start,
                        leaf, t.near_cnt.as<int64_t>(), c.tile_bucket.as<int32_t>(), order);
     LSS_CHECK_LAUNCH("order_tiles");

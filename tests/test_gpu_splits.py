@@ -149,3 +149,21 @@ def test_hessian_and_multiscale_tiles_shared_by_waves(n):
     for k, (a, b, tol) in enumerate(zip(got[1], got[0], (1e-12, 1e-12 * scale, 1e-11 * scale / sig.min(),
                                                          1e-12, 1e-12 * scale, 1e-12))):
         assert np.abs(a - b).max() <= tol, k
+
+
+def test_mixed_heavy_tiles_are_the_same_bits():
+    """Tiles taken by a whole workgroup (few targets) and by single waves (the same targets beside many of another mesh
+    of the batch, which make them light) give the same bits: the mixed projection depends on it."""
+    parts = [star_surface(13, seed=3), star_surface(12, seed=4)]
+    sig = [0.5 * triangle_diameters(v, t) for v, t in parts]
+    few = bbox_targets(parts[0][0], 5000, pad=0.1, seed=1)
+    many = bbox_targets(parts[1][0], 1_500_000, pad=0.02, seed=2)
+    b = configs.concat_batch([dict(verts=v, tris=t, sigma=s, targets=x)
+                              for (v, t), s, x in zip(parts, sig, (few, many))])
+    c = lss.Context()
+    c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+    c.set_sigma(b["sigma"])
+    c.set_options(precision=lss.MIXED, far_field=lss.FAR_FMM)
+    p0, g0 = c.eval(few, x_mesh=np.zeros(len(few), np.int32))
+    p1, g1 = c.eval(b["targets"], x_mesh=b["target_mesh"])
+    assert np.array_equal(p0, p1[:len(few)]) and np.array_equal(g0, g1[:len(few)])
