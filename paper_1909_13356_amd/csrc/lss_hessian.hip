@@ -9,6 +9,7 @@
 // k1 = K/c, k2 = F/c, k3 = G/c come from radial3 (radial_exact.h).
 // Each pair is accumulated by pair_hess (radial_exact.h).
 // Every pair uses the full kernel (no cut, no far-field expansion).
+#include <algorithm>
 #include <climits>
 
 #include "lss_internal.h"
@@ -99,7 +100,21 @@ __global__ void k_cen_boxes(int64_t ntris, const Cen *__restrict__ cen, double *
     }
 }
 
-// sigma(x) and grad sigma of one target (phase 1 of the multiscale sums).
+// The weight sums of one target (phase 1 of the multiscale sums), relative to
+// exp(-dmin / (2 sigma0^2)), dmin the squared distance of the nearest centroid
+// seen.
+struct SigSums {
+    double dmin = INFINITY, S0 = 0.0, S1 = 0.0, V0[3] = {0.0, 0.0, 0.0}, V1[3] = {0.0, 0.0, 0.0};
+    __device__ __forceinline__ void rescale(double f) {
+        S0 *= f;
+        S1 *= f;
+        for (int d = 0; d < 3; ++d) {
+            V0[d] *= f;
+            V1[d] *= f;
+        }
+    }
+};
+
 // The centroids come in runs of 256 (run r = [256 r, 256 r + 256)) with
 // bounding boxes.  A first pass bounds the nearest centroid's squared
 // distance from above by the farthest corner distance of each run that
@@ -107,11 +122,13 @@ __global__ void k_cen_boxes(int64_t ntris, const Cen *__restrict__ cen, double *
 // that bound by 100 sigma0^2 carries weights below e^-50 of the largest and
 // is skipped, and so is any single centroid that far.  The workgroup stages a run in LDS when any of its targets
 // needs it; the sums are taken relative to the nearest centroid seen so far
-// (rescaled when it changes).  Returns false (sigma = 0.5, grad = 0) for an
-// empty range.  Every thread of the workgroup must call it.
-__device__ bool sigma_phase(const Cen *__restrict__ cen, const double *__restrict__ box, Cen *ctile, long long *blo,
+// (rescaled when it changes), four centroids at a time: the exponential's chain
+// of dependent operations leaves the SIMD idle otherwise.  piece / pieces: the
+// share of the runs that is summed.  Every thread of the workgroup must call it.
+constexpr int kSigStep = 4;
+__device__ void sigma_phase(const Cen *__restrict__ cen, const double *__restrict__ box, Cen *ctile, long long *blo,
                             long long *bhi, int64_t j0, int64_t j1, double px, double py, double pz, double s0,
-                            double &sg, double gs[3]) {
+                            int piece, int pieces, SigSums &A) {
     if (threadIdx.x == 0) {
         *blo = LLONG_MAX;
         *bhi = 0;
@@ -136,8 +153,8 @@ __device__ bool sigma_phase(const Cen *__restrict__ cen, const double *__restric
         }
         dref = fmin(dref, far2);
     }
-    double dmin = INFINITY, S0 = 0.0, S1 = 0.0, V0x = 0.0, V0y = 0.0, V0z = 0.0, V1x = 0.0, V1y = 0.0, V1z = 0.0;
-    for (int64_t r = r0; r < r1; ++r) {
+    const int64_t per = (r1 - r0 + pieces - 1) / pieces, ra = r0 + piece * per, rb = ra + per < r1 ? ra + per : r1;
+    for (int64_t r = ra; r < rb; ++r) {
         bool need = j0 < (r + 1) * 256 && j1 > r * 256;
         if (need) {
             double near2 = 0.0;
@@ -153,56 +170,68 @@ __device__ bool sigma_phase(const Cen *__restrict__ cen, const double *__restric
         if (j >= lo && j < hi) ctile[threadIdx.x] = cen[j];
         __syncthreads();
         if (need) {
-            const int64_t k0 = j0 > b ? j0 - b : 0;
-            const int64_t k1 = (j1 - b < 256) ? j1 - b : 256;
-            for (int64_t k = k0; k < k1; ++k) {
-                const Cen c = ctile[k];
-                const double dx = px - c.cx, dy = py - c.cy, dz = pz - c.cz;
-                const double d2 = dx * dx + dy * dy + dz * dz;
-                if ((d2 - dref) * inv2s0 > 50.0) continue;   // weight below e^-50 of the nearest
-                if (d2 < dmin) {          // new nearest centroid: rescale the sums to it
-                    const double f = exp((d2 - dmin) * inv2s0);
-                    S0 *= f;
-                    S1 *= f;
-                    V0x *= f;
-                    V0y *= f;
-                    V0z *= f;
-                    V1x *= f;
-                    V1y *= f;
-                    V1z *= f;
-                    dmin = d2;
+            const int k0 = j0 > b ? (int)(j0 - b) : 0;
+            const int k1 = j1 - b < 256 ? (int)(j1 - b) : 256;
+            for (int k = k0; k < k1; k += kSigStep) {
+                double dx[kSigStep], dy[kSigStep], dz[kSigStep], d2[kSigStep], sj[kSigStep], dn = INFINITY;
+#pragma unroll
+                for (int q = 0; q < kSigStep; ++q) {
+                    const Cen c = ctile[k + q < k1 ? k + q : k];
+                    dx[q] = px - c.cx;
+                    dy[q] = py - c.cy;
+                    dz[q] = pz - c.cz;
+                    d2[q] = dx[q] * dx[q] + dy[q] * dy[q] + dz[q] * dz[q];
+                    sj[q] = c.sj;
+                    // past the run, or weight below e^-50 of the nearest: no weight
+                    if (k + q >= k1 || (d2[q] - dref) * inv2s0 > 50.0) d2[q] = INFINITY;
+                    dn = fmin(dn, d2[q]);
                 }
-                const double w = exp((dmin - d2) * inv2s0);
-                const double sw = c.sj * w;
-                S0 += w;
-                S1 += sw;
-                V0x += w * dx;
-                V0y += w * dy;
-                V0z += w * dz;
-                V1x += sw * dx;
-                V1y += sw * dy;
-                V1z += sw * dz;
+                if (dn < A.dmin) {            // new nearest centroid: rescale the sums to it
+                    A.rescale(exp((dn - A.dmin) * inv2s0));
+                    A.dmin = dn;
+                }
+                if (!(A.dmin < INFINITY)) continue;
+#pragma unroll
+                for (int q = 0; q < kSigStep; ++q) {
+                    const double w = exp((A.dmin - d2[q]) * inv2s0), sw = sj[q] * w;
+                    A.S0 += w;
+                    A.S1 += sw;
+                    A.V0[0] += w * dx[q];
+                    A.V0[1] += w * dy[q];
+                    A.V0[2] += w * dz[q];
+                    A.V1[0] += sw * dx[q];
+                    A.V1[1] += sw * dy[q];
+                    A.V1[2] += sw * dz[q];
+                }
             }
         }
         __syncthreads();                  // the run's LDS copy is consumed
     }
-    const bool have = S0 > 0.0;
-    sg = have ? S1 / S0 : 0.5;
-    const double gsc = have ? -1.0 / (s0 * s0 * S0) : 0.0;
-    gs[0] = gsc * (V1x - sg * V0x);
-    gs[1] = gsc * (V1y - sg * V0y);
-    gs[2] = gsc * (V1z - sg * V0z);
+}
+
+// sigma and grad sigma from the sums; false (sigma = 0.5, grad = 0) for an empty range
+__device__ __forceinline__ bool sigma_finish(const SigSums &A, double s0, double &sg, double gs[3]) {
+    const bool have = A.S0 > 0.0;
+    sg = have ? A.S1 / A.S0 : 0.5;
+    const double gsc = have ? -1.0 / (s0 * s0 * A.S0) : 0.0;
+    for (int d = 0; d < 3; ++d) gs[d] = gsc * (A.V1[d] - sg * A.V0[d]);
     return have;
 }
 
-// sigma(x) and grad sigma alone (the octree path of the multiscale sums)
+// sigma(x) and grad sigma alone (the octree path of the multiscale sums).
+// With gridDim.y > 1 the workgroups of a block of points share the runs and
+// leave their sums in part[piece][9][n] for k_sigma_merge: 1e5 points are 1.5
+// waves per SIMD, which the exponential's latency leaves idle (1e5 points and
+// 43 200 centroids, and the centroids themselves: 23 -> 11.8 ms together with
+// the four at a time).  Bound by FP64 VALU issue, about 40
+// operations per (point, centroid).
 __global__ void __launch_bounds__(256) k_sigma_field(int64_t n, const double *__restrict__ x,
                                                      const int32_t *__restrict__ xm,
                                                      const int64_t *__restrict__ tri_off,
                                                      const Cen *__restrict__ cen,
                                                      const double *__restrict__ cbox,
                                                      const double *__restrict__ sigma0, double *sig,
-                                                     double *gsig) {
+                                                     double *gsig, double *__restrict__ part) {
     __shared__ Cen ctile[256];
     __shared__ long long blo, bhi;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -216,13 +245,51 @@ __global__ void __launch_bounds__(256) k_sigma_field(int64_t n, const double *__
         pz = x[3 * i + 2];
     }
     const int64_t j0 = act ? tri_off[m] : 0, j1 = act ? tri_off[m + 1] : 0;
-    double sg, gs[3];
-    const bool have = sigma_phase(cen, cbox, ctile, &blo, &bhi, j0, j1, px, py, pz, act ? sigma0[m] : 1.0, sg, gs);
+    const double s0 = act ? sigma0[m] : 1.0;
+    SigSums A;
+    sigma_phase(cen, cbox, ctile, &blo, &bhi, j0, j1, px, py, pz, s0, blockIdx.y, gridDim.y, A);
     if (!act) return;
+    if (gridDim.y > 1) {
+        double *q = part + (int64_t)blockIdx.y * 9 * n + i;
+        q[0] = A.dmin;
+        q[n] = A.S0;
+        q[2 * n] = A.S1;
+        for (int d = 0; d < 3; ++d) {
+            q[(3 + d) * n] = A.V0[d];
+            q[(6 + d) * n] = A.V1[d];
+        }
+        return;
+    }
+    double sg, gs[3];
+    const bool have = sigma_finish(A, s0, sg, gs);
     sig[i] = have ? sg : NAN;
-    gsig[3 * i] = gs[0];
-    gsig[3 * i + 1] = gs[1];
-    gsig[3 * i + 2] = gs[2];
+    for (int d = 0; d < 3; ++d) gsig[3 * i + d] = gs[d];
+}
+
+// the pieces' sums of a point, brought to the nearest centroid of all, in piece order
+__global__ void __launch_bounds__(256) k_sigma_merge(int64_t n, int pieces, const int32_t *__restrict__ xm,
+                                                     const double *__restrict__ sigma0,
+                                                     const double *__restrict__ part, double *sig, double *gsig) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const double s0 = sigma0[xm ? xm[i] : 0], inv2s0 = 0.5 / (s0 * s0);
+    SigSums A;
+    for (int k = 0; k < pieces; ++k) A.dmin = fmin(A.dmin, part[(int64_t)k * 9 * n + i]);
+    for (int k = 0; k < pieces; ++k) {
+        const double *q = part + (int64_t)k * 9 * n + i;
+        if (!(q[0] < INFINITY)) continue;           // no weight in this piece
+        const double f = exp((A.dmin - q[0]) * inv2s0);
+        A.S0 += f * q[n];
+        A.S1 += f * q[2 * n];
+        for (int d = 0; d < 3; ++d) {
+            A.V0[d] += f * q[(3 + d) * n];
+            A.V1[d] += f * q[(6 + d) * n];
+        }
+    }
+    double sg, gs[3];
+    const bool have = sigma_finish(A, s0, sg, gs);
+    sig[i] = have ? sg : NAN;
+    for (int d = 0; d < 3; ++d) gsig[3 * i + d] = gs[d];
 }
 
 // Target-attached width (section 2, eq. basemodelk, convkernel, sigma2).
@@ -262,7 +329,9 @@ __global__ void __launch_bounds__(256) k_eval_multiscale(int64_t n, const double
     // ---- phase 1: sigma(x) and its gradient
     int64_t j0 = act ? tri_off[m] : 0, j1 = act ? tri_off[m + 1] : 0;
     double sg, gs[3];
-    const bool have = sigma_phase(cen, cbox, ctile, &blo, &bhi, j0, j1, px, py, pz, act ? sigma0[m] : 1.0, sg, gs);
+    SigSums sums;
+    sigma_phase(cen, cbox, ctile, &blo, &bhi, j0, j1, px, py, pz, act ? sigma0[m] : 1.0, 0, 1, sums);
+    const bool have = sigma_finish(sums, act ? sigma0[m] : 1.0, sg, gs);
     const double gsx = gs[0], gsy = gs[1], gsz = gs[2];
     int64_t lo, hi;
     // ---- phase 2: Phi, grad Phi with width sigma(x)
@@ -422,8 +491,16 @@ void launch_cen_boxes(Ctx &c, const Cen *cen, double *box) {
 
 void launch_sigma_field(Ctx &c, int64_t n, const double *x, const int32_t *xm, const Cen *cen, const double *cbox,
                         const double *sigma0, double *sig, double *gsig) {
-    hipLaunchKernelGGL(k_sigma_field, dim3(blocks256(n)), dim3(256), 0, c.stream, n, x, xm, c.tri_off.as<int64_t>(),
-                       cen, cbox, sigma0, sig, gsig);
+    // few points: split the runs until about 8192 waves run (five per SIMD are
+    // resident), a run each at least
+    const int64_t runs = (c.ntris + 255) / 256, waves = 4 * (int64_t)blocks256(n);
+    const int pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(8192 / waves, runs), 256));
+    if (pieces > 1) c.sig_part.ensure(sizeof(double) * 9 * (size_t)n * pieces);
+    hipLaunchKernelGGL(k_sigma_field, dim3(blocks256(n), pieces), dim3(256), 0, c.stream, n, x, xm,
+                       c.tri_off.as<int64_t>(), cen, cbox, sigma0, sig, gsig, c.sig_part.as<double>());
+    if (pieces > 1)
+        hipLaunchKernelGGL(k_sigma_merge, dim3(blocks256(n)), dim3(256), 0, c.stream, n, pieces, xm, sigma0,
+                           c.sig_part.as<double>(), sig, gsig);
     LSS_CHECK_LAUNCH("k_sigma_field");
 }
 

@@ -167,3 +167,22 @@ def test_mixed_heavy_tiles_are_the_same_bits():
     p0, g0 = c.eval(few, x_mesh=np.zeros(len(few), np.int32))
     p1, g1 = c.eval(b["targets"], x_mesh=b["target_mesh"])
     assert np.array_equal(p0, p1[:len(few)]) and np.array_equal(g0, g1[:len(few)])
+
+
+@pytest.mark.parametrize("n", [1, 255, 4000, 600_000])
+def test_sigma_field_pieces(n):
+    """sigma(x) by the direct sum, its centroid runs split over workgroups (few points) and not (6e5), on a ragged pair
+    of meshes with runs that straddle them, against the oracle on a sample (1e-12 relative)."""
+    parts = [star_surface(9, seed=1), star_surface(5, seed=2)]
+    meshes = [dict(verts=v, tris=t, sigma=0.5 * triangle_diameters(v, t), targets=bbox_targets(v, m, pad=0.5, seed=m))
+              for (v, t), m in zip(parts, (n, n // 2 + 1))]
+    b = configs.concat_batch(meshes)
+    c = lss.Context()
+    c.set_options(far_field=lss.FAR_FMM, sigma_interp=1)
+    c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+    sig = c.eval_multiscale(b["targets"], 2.5, 0.07, x_mesh=b["target_mesh"])[2]
+    k = np.unique(np.linspace(0, len(sig) - 1, 300).astype(int))
+    want = oracle.sigma_field(b["verts"], b["tris"], b["targets"][k], 2.5, 0.07, tri_offsets=b["tri_offsets"],
+                              x_mesh=b["target_mesh"][k])
+    want = want[0] if isinstance(want, tuple) else want
+    assert np.abs(sig[k] / want - 1.0).max() <= 1e-12
