@@ -389,7 +389,7 @@ int lss_chart_curvature(lss_ctx *ctx, const double *chart_uv, int32_t np, const 
  * every triangle (index j * np + i, e.g. x or h from lss_project); eval_uv
  * (ne,2) points of the simplex; out (ntris*ne, ncomp) receives the value of
  * every triangle's degree-p interpolant at them (index j * ne + e).  The
- * interpolation matrix (ne x np) is formed on the host in FP64 by LU with
+ * interpolation matrix (ne x np) is formed in FP64 by elimination with
  * partial pivoting; one kernel applies it to all triangles.  Needs sources
  * (LSS_ESTATE otherwise), not sigma.  Host or device arrays as for
  * lss_project; returns when out is written. */

@@ -291,6 +291,7 @@ struct Ctx {
     DBuf tflag, tpos, tstart, ntiles, tleaf;   // FMM eval: leaf of each sorted target, tile heads
     DBuf pairs;               // double accumulator of executed pairs (stats)
     DBuf sig_part;            // partial weight sums of sigma(x)
+    DBuf interp_mat;          // chart interpolation matrix and its singularity flag
     DBuf part;                // partial sums of a direct evaluation whose nodes are split
     DBuf tile_queue;          // uint32[4] work queue of the FMM evaluation (zero between launches)
     DBuf tile_order;          // FMM tiles, most expensive first (int32 per tile)

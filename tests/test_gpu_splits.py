@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import paper_1909_13356_amd as lss
-from workloads import dunavant6, cube_mesh, star_surface, triangle_diameters, bbox_targets, configs
+from workloads import dunavant6, cube_mesh, star_surface, triangle_diameters, bbox_targets, chart_nodes, configs
 
 pytestmark = pytest.mark.gpu
 
@@ -186,3 +186,33 @@ def test_sigma_field_pieces(n):
                               x_mesh=b["target_mesh"][k])
     want = want[0] if isinstance(want, tuple) else want
     assert np.abs(sig[k] / want - 1.0).max() <= 1e-12
+
+
+@pytest.mark.parametrize("p,ne,ncomp,n,bad", [(0, 1, 1, 2, False), (1, 16, 3, 4, False), (4, 17, 2, 5, True), (8, 66, 3, 7, True),
+                                              (8, 81, 16, 3, False), (5, 700, 5, 3, True), (19, 33, 1, 3, False),
+                                              (19, 200, 10, 2, True), (19, 9, 15, 2, False), (8, 66, 3, 40, False), (9, 20, 3, 4, True), (14, 33, 1, 3, False),
+                                              (15, 33, 1, 3, False)])
+def test_chart_interp_tiles(p, ne, ncomp, n, bad):
+    """Chart interpolation at the edges of the matrix tiles: one point and one node, a full tile, remainders in points,
+    nodes and columns, points shared by workgroups, the matrix from memory, a triangle too large for LDS.  A node that
+    is not finite stays with its own triangle and component.  Bound: both solve with V, so 64 ulp
+    times its condition number, relative to the sums of magnitudes."""
+    v, t = star_surface(n, seed=n)
+    c = lss.Context()
+    c.set_sources(v, t, dunavant6())
+    uv = chart_nodes(p) if p else np.array([[0.3, 0.3]])
+    rng = np.random.default_rng(ne)
+    ev = rng.dirichlet([1, 1, 1], ne)[:, :2]
+    f = rng.standard_normal((len(t) * len(uv), ncomp))
+    if bad:
+        f[len(uv) // 2, ncomp - 1], f[-1, 0] = np.nan, np.inf
+    got = c.chart_interp(uv, f, ev)
+    I = oracle.chart_interp(uv, np.eye(len(uv)).reshape(-1), ev).reshape(len(uv), ne).T      # one triangle per node
+    ff = f.reshape(len(t), len(uv), ncomp)
+    want = np.einsum("ei,jic->jec", I, np.where(np.isfinite(ff), ff, 0.0))
+    scale = np.einsum("ei,jic->jec", np.abs(I), np.where(np.isfinite(ff), np.abs(ff), 0.0)).max()
+    hit = ~np.isfinite(ff).all(axis=1)                                                       # (triangle, component)
+    got = got.reshape(len(t), ne, ncomp)
+    mask = np.broadcast_to(hit[:, None, :], got.shape)
+    assert np.all(np.isfinite(got[~mask])) and not np.any(np.isfinite(got[mask]))
+    assert np.abs(got - want)[~mask].max() <= 64 * 2.0 ** -52 * np.linalg.cond(oracle.koornwinder(uv, p)) * scale
