@@ -153,7 +153,10 @@ __device__ __forceinline__ void pair64(const Src &s, double x, double y, double 
 }
 
 // K consecutive FP64 records against one target (see nodes32 below); with
-// COUNT the pairs inside the cut are added to *cnt
+// COUNT the pairs inside the cut are added to *cnt.  Neither form's argument
+// is clamped to its side of the cut: the form of the other side is not
+// selected, whatever it came out as (1 to 3 instructions of 33 to 75 a pair;
+// 1.7e7 pairs of a small direct sum 466 -> 454 us).
 template <int K, bool COUNT = false>
 __device__ __forceinline__ void nodes64(const Src *sh, double x, double y, double z, double &p, double &gx,
                                         double &gy, double &gz, uint32_t *cnt = nullptr) {
@@ -169,8 +172,7 @@ __device__ __forceinline__ void nodes64(const Src *sh, double x, double y, doubl
         ad[k] = fma(s.ax, dx[k], fma(s.ay, dy[k], s.az * dz[k]));
         u[k] = r2 * s.s2;
         umin = fmin(umin, u[k]);
-        const double ux = fmax(u[k], KF64_X);
-        const double r = rsq64(ux);
+        const double r = rsq64(u[k]);       // inside the cut replaced below
         const double rr = r * r;
         S[k] = rr * r;                      // folded far form (see fold_src)
         T[k] = S[k] * rr;
@@ -178,7 +180,7 @@ __device__ __forceinline__ void nodes64(const Src *sh, double x, double y, doubl
     if (umin < KF64_X) {                    // some pair of the group inside the cut
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const double t = fmin(u[k], KF64_X) * KF64_INV_X;
+            const double t = u[k] * KF64_INV_X;     // beyond the cut not selected
             double ps = kf64_ps[KF64_Q_DEG], pt = kf64_pt[KF64_Q_DEG], q = kf64_q[KF64_Q_DEG];
 #pragma unroll
             for (int i = KF64_Q_DEG - 1; i >= 0; --i) {
@@ -270,6 +272,8 @@ __device__ __forceinline__ void pair_far64(const FarD &s, double x, double y, do
 
 constexpr int kNodeGroup = 4;
 
+// K consecutive FP32 records against one target, as nodes64 (unclamped
+// arguments: 2e5 targets x 38 000 nodes 49.2 -> 48.2 ms)
 template <int K, bool COUNT = false>
 __device__ __forceinline__ void nodes32(const SrcF *sh, float x, float y, float z, float xl, float yl, float zl,
                                         float &p, float &gx, float &gy, float &gz, uint32_t *cnt = nullptr) {
@@ -285,7 +289,7 @@ __device__ __forceinline__ void nodes32(const SrcF *sh, float x, float y, float 
         ad[k] = fmaf(s.ax, dx[k], fmaf(s.ay, dy[k], s.az * dz[k]));
         u[k] = r2 * s.s2;
         umin = fminf(umin, u[k]);
-        const float r = __builtin_amdgcn_rsqf(fmaxf(u[k], (float)KF32_X));
+        const float r = __builtin_amdgcn_rsqf(u[k]);    // inside the cut replaced below
         const float rr = r * r;
         S[k] = rr * r;                      // folded far form (see SrcF)
         T[k] = S[k] * rr;
@@ -293,7 +297,7 @@ __device__ __forceinline__ void nodes32(const SrcF *sh, float x, float y, float 
     if (umin < (float)KF32_X) {             // some pair of the group inside the cut
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const float t = fminf(u[k], (float)KF32_X) * (float)KF32_INV_X;
+            const float t = u[k] * (float)KF32_INV_X;       // beyond the cut not selected
             float ps = kf32_ps[KF32_PS_DEG], pt = kf32_pt[KF32_PT_DEG], q = kf32_q[KF32_Q_DEG];
 #pragma unroll
             for (int i = KF32_Q_DEG - 1; i >= 0; --i) {
