@@ -272,16 +272,52 @@ __device__ __forceinline__ void pair_far64(const FarD &s, double x, double y, do
 
 constexpr int kNodeGroup = 4;
 
-// K consecutive FP32 records against one target, as nodes64 (unclamped
-// arguments: 2e5 targets x 38 000 nodes 49.2 -> 48.2 ms)
-template <int K, bool COUNT = false>
-__device__ __forceinline__ void nodes32(const SrcF *sh, float x, float y, float z, float xl, float yl, float zl,
+// The direct sum's records in LDS: groups of four nodes, component by
+// component, so that every read is a full 16 bytes.  A 12-byte read
+// (ds_read_b96) holds the LDS for 8.1 cycles, a 16-byte one for 4.4, and a
+// SrcF read in three pieces has two of the former: 82 LDS cycles of a CU for
+// four nodes and a wave, where the VALU needs 95; 48 as a group.  2.5e5
+// targets x 242 000 nodes: 48.2 -> 46.6 ms, 1.3e12 pairs/s, now bound by VALU
+// issue (1.5e12 at the clock it runs at).  (The octree
+// kernels keep SrcF: there a node meets fewer targets, and writing eleven
+// pieces costs what reading them saves.)
+struct NearGroup {
+    float __attribute__((ext_vector_type(4))) v[11];     // yx yy yz lx ly lz s2 ax ay az s2x2
+};
+__device__ __forceinline__ void put(NearGroup *sh, int i, const SrcF &f) {
+    float *b = reinterpret_cast<float *>(sh + i / kNodeGroup) + i % kNodeGroup;
+    const float c[11] = {f.yx, f.yy, f.yz, f.lx, f.ly, f.lz, f.s2, f.ax, f.ay, f.az, f.s2x2};
+#pragma unroll
+    for (int k = 0; k < 11; ++k) b[kNodeGroup * k] = c[k];
+}
+__device__ __forceinline__ SrcF record(const SrcF *sh, int k) { return sh[k]; }
+__device__ __forceinline__ SrcF record(const NearGroup *sh, int k) {
+    const NearGroup &g = sh[k / kNodeGroup];
+    const int j = k % kNodeGroup;
+    SrcF f;
+    f.yx = g.v[0][j];
+    f.yy = g.v[1][j];
+    f.yz = g.v[2][j];
+    f.lx = g.v[3][j];
+    f.ly = g.v[4][j];
+    f.lz = g.v[5][j];
+    f.s2 = g.v[6][j];
+    f.ax = g.v[7][j];
+    f.ay = g.v[8][j];
+    f.az = g.v[9][j];
+    f.s2x2 = g.v[10][j];
+    return f;
+}
+
+// K consecutive FP32 records against one target, as nodes64
+template <int K, bool COUNT = false, class Rec>
+__device__ __forceinline__ void nodes32(const Rec *sh, float x, float y, float z, float xl, float yl, float zl,
                                         float &p, float &gx, float &gy, float &gz, uint32_t *cnt = nullptr) {
     float dx[K], dy[K], dz[K], u[K], ad[K], S[K], T[K];
     float umin = 3.0e38f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const SrcF s = sh[k];
+        const SrcF s = record(sh, k);
         dx[k] = (x - s.yx) + (xl - s.lx);
         dy[k] = (y - s.yy) + (yl - s.ly);
         dz[k] = (z - s.yz) + (zl - s.lz);
@@ -314,7 +350,7 @@ __device__ __forceinline__ void nodes32(const SrcF *sh, float x, float y, float 
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const SrcF &s = sh[k];
+        const SrcF s = record(sh, k);
         const float g = ad[k] * T[k] * s.s2x2;
         p = fmaf(-ad[k], S[k], p);
         gx = fmaf(g, dx[k], fmaf(-s.ax, S[k], gx));
@@ -653,7 +689,7 @@ __global__ __launch_bounds__(TILE) void k_p2p_direct_mixed(
     const double *__restrict__ ty, const double *__restrict__ tz, const int32_t *__restrict__ tmesh,
     const int64_t *__restrict__ node_off, const Src *__restrict__ src, const int32_t *__restrict__ out_idx,
     double *__restrict__ phi, double *__restrict__ grad, double *__restrict__ pairs, float *__restrict__ part) {
-    __shared__ SrcF sh[TILE];
+    __shared__ NearGroup sh[TILE / kNodeGroup];
     const int64_t n = n_dev ? (int64_t)*n_dev : nmax;
     const int64_t t0 = (int64_t)blockIdx.x * TILE;
     if (t0 >= n) return;
@@ -697,8 +733,7 @@ __global__ __launch_bounds__(TILE) void k_p2p_direct_mixed(
             } else {
                 f = pad_srcf();
             }
-            f.pad = 0.0f;
-            sh[lane] = f;
+            put(sh, lane, f);
         }
         __syncthreads();
         if (!live) continue;
@@ -711,10 +746,10 @@ __global__ __launch_bounds__(TILE) void k_p2p_direct_mixed(
             float p = 0, gx = 0, gy = 0, gz = 0;
             const int j1 = j0 + 32 < cnt ? j0 + 32 : cnt;
             if (wave_full) {                // chunk padded with zero records to whole node groups
-                for (int j = j0; j < j1; j += kNodeGroup) nodes32<kNodeGroup>(sh + j, x, y, z, xl, yl, zl, p, gx, gy, gz);
+                for (int j = j0; j < j1; j += kNodeGroup) nodes32<kNodeGroup>(sh + j / kNodeGroup, x, y, z, xl, yl, zl, p, gx, gy, gz);
             } else {
                 const int a0 = j0 > jb ? j0 : jb, a1 = j1 < je ? j1 : je;
-                for (int j = a0; j < a1; ++j) pair32(sh[j], x, y, z, xl, yl, zl, p, gx, gy, gz);
+                for (int j = a0; j < a1; ++j) pair32(record(sh, j), x, y, z, xl, yl, zl, p, gx, gy, gz);
             }
             two_sum_f(sp, ep, p);
             two_sum_f(sx, ex, gx);
