@@ -388,6 +388,10 @@ void launch_newton_output(Ctx &c, int64_t N, double *h, double *xout, int8_t *st
 inline int fmm_order_for(const Ctx &c) {
     return c.opt.fmm_order > 0 ? c.opt.fmm_order : (c.opt.precision == LSS_MIXED ? 20 : 26);
 }
+// The form of M2L of this build (lss_fmm.hip): rotated operators, all pairs in
+// one plan, wherever the near field is summed in FP64, that is in FP64 contexts
+// and for the target-attached width; by displacement class in mixed contexts.
+inline bool m2l_rotated(const Ctx &c) { return c.opt.precision != LSS_MIXED || c.target_widths; }
 // the boxes (levels, radii, target cuts), then the interaction lists
 void build_tree_boxes(Ctx &c);
 void build_tree_lists(Ctx &c);     // dual traversal; mixed: the M2L list sorted by class

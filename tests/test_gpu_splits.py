@@ -216,3 +216,21 @@ def test_chart_interp_tiles(p, ne, ncomp, n, bad):
     mask = np.broadcast_to(hit[:, None, :], got.shape)
     assert np.all(np.isfinite(got[~mask])) and not np.any(np.isfinite(got[mask]))
     assert np.abs(got - want)[~mask].max() <= 64 * 2.0 ** -52 * np.linalg.cond(oracle.koornwinder(uv, p)) * scale
+
+
+@pytest.mark.parametrize("n", [2, 17])
+def test_m2l_forms_alternate(n):
+    """A mixed context's field (M2L by class) before and after a target-attached evaluation (one plan of all pairs, also
+    where there is no pair at all): the same bit for bit, and the latter against the direct sum (1e-7, its cut)."""
+    v, t = star_surface(n, seed=n)
+    x = bbox_targets(v, 800, pad=0.2, seed=3)
+    c = lss.Context()
+    c.set_options(precision=lss.MIXED, far_field=lss.FAR_FMM)
+    c.set_sources(v, t, dunavant6())
+    c.set_sigma(0.5 * triangle_diameters(v, t))
+    before = c.eval(x)
+    ms = c.eval_multiscale(x, 2.5, 0.0)
+    after = c.eval(x)
+    assert all(np.array_equal(a, b) for a, b in zip(before, after))
+    want = oracle.evaluate_multiscale(v, t, dunavant6(), x, 2.5, 0.0)
+    assert np.abs(ms[0] - want[0]).max() <= 1e-7
