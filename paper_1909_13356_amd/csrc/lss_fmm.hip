@@ -501,8 +501,94 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
 }
 
+// The same translations for launches that do not fill the chip, whose time is
+// the chain of one workgroup's steps: 16 rows x 64 pairs (one accumulator tile
+// per wave, a quarter of the chain's products, four times the workgroups) and
+// kKS coefficients per step, so that fewer and longer fetches stand in the
+// chain.  The products of an output are added in the same order: the result is
+// that of k_gemm bit for bit.  Two steps' fetches are on their way.  M2M of a
+// small tree at p = 26 (5832 coefficients a parent) 280 -> 131 us a level, L2L
+// 40 -> 26, M2L of a class of 500 to 2000 pairs 26 -> 11 to 28.
+constexpr int kKS = 32;
+// 64 x 64 workgroups of a launch below which it is short: at 300 to 400 both
+// forms take 35 to 45 us a launch (p = 20), at 150 to 200 this one 23 and
+// k_gemm 33 to 44
+constexpr int64_t kShortLaunch = 256;
+__global__ __launch_bounds__(256) void k_gemm_short(GemmArgs a) {
+    __shared__ double As[kKS][17];
+    __shared__ double Bs[kKS][65];
+    __shared__ int64_t scol[64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int r0 = blockIdx.x * 16;
+    const int64_t j0 = (int64_t)blockIdx.y * 64;
+    const int oct = blockIdx.z;
+    const double *__restrict__ op = a.opT + (int64_t)oct * a.ncp * a.ncp;
+    if (threadIdx.x < 64) {
+        int64_t j = j0 + threadIdx.x, d, col;
+        double sc;
+        if (j < a.npairs) { pair_of(a, j, oct, d, col, sc); scol[threadIdx.x] = col; }
+        else scol[threadIdx.x] = -1;
+    }
+    __syncthreads();
+    // per thread: A elements (k, r) = (tid / 16 + 16 i, tid % 16), B elements of the columns
+    // tid / kKS + (256 / kKS) i at k = tid % kKS (a wave reads along a column)
+    constexpr int kNA = kKS / 16, kNB = kKS / 4, kStep = 256 / kKS;
+    const int ar = threadIdx.x & 15, ak = threadIdx.x >> 4, bk = threadIdx.x % kKS, bc = threadIdx.x / kKS;
+    const bool arow = r0 + ar < a.rows;
+    double ra[2][kNA], rb[2][kNB];
+    int64_t cols[kNB];
+#pragma unroll
+    for (int i = 0; i < kNB; ++i) cols[i] = scol[bc + kStep * i];
+    auto fetch = [&](int k0, double (&fa)[kNA], double (&fb)[kNB]) {
+#pragma unroll
+        for (int i = 0; i < kNA; ++i) {
+            const int k = k0 + ak + 16 * i;
+            fa[i] = arow && k < a.nk ? op[(int64_t)k * a.ncp + r0 + ar] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < kNB; ++i) fb[i] = cols[i] >= 0 && k0 + bk < a.nk ? a.X[cols[i] + k0 + bk] : 0.0;
+    };
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    auto step = [&](int k0, double (&fa)[kNA], double (&fb)[kNB]) {
+        __syncthreads();                                   // previous block's MFMAs are done with LDS
+#pragma unroll
+        for (int i = 0; i < kNA; ++i) As[ak + 16 * i][ar] = fa[i];
+#pragma unroll
+        for (int i = 0; i < kNB; ++i) Bs[bk][bc + kStep * i] = fb[i];
+        __syncthreads();
+        fetch(k0 + 2 * kKS, fa, fb);                       // zeros past the end
+#pragma unroll
+        for (int kk = 0; kk < kKS; kk += 4)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(As[kk + (lane >> 4)][lane & 15], Bs[kk + (lane >> 4)][16 * w + (lane & 15)],
+                                                       acc, 0, 0, 0);
+    };
+    fetch(0, ra[0], rb[0]);
+    fetch(kKS, ra[1], rb[1]);
+    for (int k0 = 0; k0 < a.nk; k0 += 2 * kKS) {
+        step(k0, ra[0], rb[0]);
+        if (k0 + kKS < a.nk) step(k0 + kKS, ra[1], rb[1]);
+    }
+    const int64_t j = j0 + 16 * w + (lane & 15);
+    if (j >= a.npairs) return;
+    int64_t d, col;
+    double sc;
+    pair_of(a, j, oct, d, col, sc);
+    double *y = a.Y + d * a.ncp;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int row = r0 + (lane >> 4) + 4 * q;
+        if (row < a.rows) y[row] += sc * acc[q];
+    }
+}
+
 void gemm(Ctx &c, GemmArgs a) {
     if (a.rows <= 0) a.rows = a.ncp;
+    if (a.npairs > 0 && ceil_div(a.rows, kTR) * ceil_div(a.npairs, 64) * (a.mode == G_L2L ? 8 : 1) < kShortLaunch) {
+        const dim3 grid((unsigned)ceil_div(a.rows, 16), (unsigned)ceil_div(a.npairs, 64), a.mode == G_L2L ? 8u : 1u);
+        hipLaunchKernelGGL(k_gemm_short, grid, dim3(256), 0, c.stream, a);
+        LSS_CHECK_LAUNCH("k_gemm_short");
+        return;
+    }
     // short lists (fewer than four 128-pair workgroups per CU) take 64-pair workgroups
     const bool small = a.npairs * (a.mode == G_L2L ? 8 : 1) * ceil_div(a.rows, kTR) < 4 * 256 * 128;
     const int tp = small ? 64 : 128;

@@ -234,3 +234,26 @@ def test_m2l_forms_alternate(n):
     assert all(np.array_equal(a, b) for a, b in zip(before, after))
     want = oracle.evaluate_multiscale(v, t, dunavant6(), x, 2.5, 0.0)
     assert np.abs(ms[0] - want[0]).max() <= 1e-7
+
+
+@pytest.mark.parametrize("precision,order", [(lss.FP64, 26), (lss.FP64, 9), (lss.MIXED, 20), (lss.MIXED, 6)])
+def test_translation_launch_sizes(precision, order):
+    """The far field of one small surface (short translation launches, contraction lengths that end inside a step) and
+    of 40 copies of it in one context (long ones): the products are the same, summed in the same order but for the
+    classes that change their form with the number of pairs (1e-13 of the largest value)."""
+    v, t = star_surface(10, seed=6)
+    sig = 0.5 * triangle_diameters(v, t)
+    x = bbox_targets(v, 500, pad=0.1, seed=2)
+    one = dict(verts=v, tris=t, sigma=sig, targets=x)
+    b = configs.concat_batch([one] * 40)
+    out = []
+    for m in (one, b):
+        c = lss.Context()
+        c.set_options(precision=precision, far_field=lss.FAR_FMM, fmm_order=order)
+        kw = {} if m is one else dict(tri_offsets=b["tri_offsets"])
+        c.set_sources(m["verts"], m["tris"], dunavant6(), **kw)
+        c.set_sigma(m["sigma"])
+        out.append(c.eval(m["targets"], **({} if m is one else dict(x_mesh=b["target_mesh"]))))
+    for a, w in zip(out[0], out[1]):
+        w = w.reshape((40,) + a.shape)
+        assert np.abs(w - a[None]).max() <= 1e-13 * np.abs(a).max()
