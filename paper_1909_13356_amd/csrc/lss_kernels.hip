@@ -92,7 +92,7 @@ __global__ void k_prep_sources(int64_t nnodes, int32_t nq, const double *__restr
     r.ax = cnorm * w * J[0];
     r.ay = cnorm * w * J[1];
     r.az = cnorm * w * J[2];
-    r.s2x2 = 2.0 * r.s2;
+    r.fold = kFoldA / (r.s2 * sqrt(r.s2));
     out[k] = r;
 }
 

@@ -33,20 +33,13 @@ namespace lss {
 
 namespace {
 
-constexpr double kSqrtPiHalf = 0.88622692545275801365;
-// Staged node records carry the far-form constants: a' times kFoldA and 2 s2
-// times kFoldT (SrcF, fold_src), so that the pair kernels work with
-// S / (sqrt(pi)/2) and T / (1.5 sqrt(pi)/2); the fits below the cut
-// (kfit_tables.h) are generated for these quotients.
-constexpr double kFoldA = kSqrtPiHalf, kFoldT = 1.5;
-
 // FP64 node record as staged in LDS: the far-form constants folded in as in
 // SrcF (a' times sqrt(pi)/2, 2 s2 times 1.5)
 __device__ __forceinline__ Src fold_src(Src f) {
     f.ax *= kFoldA;
     f.ay *= kFoldA;
     f.az *= kFoldA;
-    f.s2x2 *= kFoldT;
+    f.fold = kFoldT * (2.0 * f.s2);
     return f;
 }
 
@@ -57,7 +50,7 @@ __device__ __forceinline__ Src fold_src(Src f) {
 __device__ __forceinline__ Src pad_src() {
     Src f;
     f.yx = f.yy = f.yz = 1.0e150;
-    f.ax = f.ay = f.az = f.s2x2 = 0.0;
+    f.ax = f.ay = f.az = f.fold = 0.0;
     f.s2 = 1.0;
     return f;
 }
@@ -146,7 +139,7 @@ __device__ __forceinline__ void pair64(const Src &s, double x, double y, double 
     double S, T;
     kfun64(r2 * s.s2, S, T);
     p = fma(-ad, S, p);
-    const double g = ad * T * s.s2x2;
+    const double g = ad * T * s.fold;
     gx = fma(g, dx, fma(-s.ax, S, gx));
     gy = fma(g, dy, fma(-s.ay, S, gy));
     gz = fma(g, dz, fma(-s.az, S, gz));
@@ -201,7 +194,7 @@ __device__ __forceinline__ void nodes64(const Src *sh, double x, double y, doubl
     for (int k = 0; k < K; ++k) {
         const Src &s = sh[k];
         p = fma(-ad[k], S[k], p);
-        const double g = ad[k] * T[k] * s.s2x2;
+        const double g = ad[k] * T[k] * s.fold;
         gx = fma(g, dx[k], fma(-s.ax, S[k], gx));
         gy = fma(g, dy[k], fma(-s.ay, S[k], gy));
         gz = fma(g, dz[k], fma(-s.az, S[k], gz));
@@ -729,7 +722,7 @@ __global__ __launch_bounds__(TILE) void k_p2p_direct_mixed(
                 f.ax = (float)(kFoldA * s.ax);
                 f.ay = (float)(kFoldA * s.ay);
                 f.az = (float)(kFoldA * s.az);
-                f.s2x2 = (float)(kFoldT * s.s2x2);
+                f.s2x2 = (float)(kFoldT * (2.0 * s.s2));
             } else {
                 f = pad_srcf();
             }
@@ -1584,7 +1577,7 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
             } else if (isfar) {
                 int pos = hf + nf + below(fm);
                 if (pos >= kRing64) pos -= kRing64;
-                const double fa = kFoldA / (sr.s2 * sqrt(sr.s2));     // a'' (nodes64_far)
+                const double fa = sr.fold;            // a'' (nodes64_far)
                 FarD f;
                 f.yx = sr.yx;
                 f.yy = sr.yy;
@@ -1755,7 +1748,7 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
                 if (lane < cnt && !isfar) {
                     sh[below(nm)] = sr;
                 } else if (isfar) {
-                    const double fa = kFoldA / (sr.s2 * sqrt(sr.s2));     // a''
+                    const double fa = sr.fold;            // a''
                     FarD f;
                     f.yx = sr.yx;
                     f.yy = sr.yy;
@@ -1971,12 +1964,12 @@ __device__ __forceinline__ SrcF mixed_near(const Src &sr, double qx, double qy, 
     f.ax = (float)(kFoldA * sr.ax);
     f.ay = (float)(kFoldA * sr.ay);
     f.az = (float)(kFoldA * sr.az);
-    f.s2x2 = (float)(kFoldT * sr.s2x2);
+    f.s2x2 = (float)(kFoldT * (2.0 * sr.s2));
     f.pad = 0.0f;
     return f;
 }
 __device__ __forceinline__ FarF mixed_far(const Src &sr, double qx, double qy, double qz) {
-    const double fa = kFoldA / (sr.s2 * sqrt(sr.s2));     // a'' (nodes32_far)
+    const double fa = sr.fold;            // a'' (nodes32_far)
     FarF f;
     f.yx = (float)qx;
     f.yy = (float)qy;
