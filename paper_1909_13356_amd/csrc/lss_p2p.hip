@@ -1392,14 +1392,28 @@ __device__ __forceinline__ int wave_ranges(const FmmEvalArgs &a, RangeList &rl, 
     return rl.off[nr];
 }
 
-// node index of packed position v (v < total)
-__device__ __forceinline__ int64_t range_node(const RangeList &rl, int nr, int v) {
-    int lo = 0, hi = nr;                       // last r with off[r] <= v
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (rl.off[mid] <= v) lo = mid; else hi = mid;
+// node index of packed position first + lane, for `width` positions from first on
+// (uniform; all lanes take part, those past the list's end get no node).  The
+// lanes look at one range each: the range of c0 is a count of the ranges that
+// end before it, and the few ranges that begin among the positions are gone
+// through one by one.  (A binary search per lane, six dependent LDS reads and
+// thirty operations for 64 nodes, made octree evaluations 1% slower.)
+__device__ __forceinline__ int64_t range_node(const RangeList &rl, int nr, int first, int width) {
+    const int c0 = __builtin_amdgcn_readfirstlane(first);
+    const int t = threadIdx.x & 63, v = c0 + t, bound = rl.off[t + 1];
+    const int64_t base = rl.beg[t] - rl.off[t];
+    auto base_of = [&](int q) {
+        return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(base >> 32), q) << 32 |
+                         (uint32_t)__builtin_amdgcn_readlane((int)base, q));
+    };
+    int q = min(__popcll(__ballot(bound <= c0)), nr - 1);
+    int64_t node = base_of(q) + v;
+    for (int next = __builtin_amdgcn_readlane(bound, q); next < c0 + width && q + 1 < nr;
+         next = __builtin_amdgcn_readlane(bound, q)) {
+        ++q;
+        if (v >= next) node = base_of(q) + v;
     }
-    return rl.beg[lo] + (v - rl.off[lo]);
+    return node;
 }
 
 // bounding box of the wave's targets, lanes past the tile end holding its
@@ -1563,8 +1577,9 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
             const int cnt = last ? 0 : (total - c0 < kRun64 ? total - c0 : kRun64);
             Src sr;
             bool isfar = false;
+            const int64_t node = last ? 0 : range_node(rl, nr, c0, kRun64);
             if (lane < cnt) {
-                sr = a.src[range_node(rl, nr, c0 + lane)];
+                sr = a.src[node];
                 isfar = box_gap2(box, sr.yx, sr.yy, sr.yz) * sr.s2 >= far_u;
             }
             c0 += W * kRun64;
@@ -1739,8 +1754,9 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
                 const int cnt = total - c0 < 64 ? total - c0 : 64;
                 Src sr;
                 bool isfar = false;
+                const int64_t node = range_node(rl, nr, c0, 64);
                 if (lane < cnt) {
-                    sr = a.src[range_node(rl, nr, c0 + lane)];
+                    sr = a.src[node];
                     isfar = box_gap2(box, sr.yx, sr.yy, sr.yz) * sr.s2 >= far_t;
                 }
                 const uint64_t fm = __ballot(isfar), nm = __ballot(lane < cnt && !isfar);
@@ -1851,8 +1867,9 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
                 const int cnt = total - c0 < 64 ? total - c0 : 64;
                 Src r;
                 bool isfar = false;
+                const int64_t node = range_node(rl, nr, c0, 64);
                 if (lane < cnt) {
-                    r = a.src[range_node(rl, nr, c0 + lane)];
+                    r = a.src[node];
                     isfar = box_gap2(box, r.yx, r.yy, r.yz) * s2min >= far_t;
                 }
                 const uint64_t fm = __ballot(isfar), nm = __ballot(lane < cnt && !isfar);
@@ -2029,8 +2046,9 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
                     Src sr;
                     double qx = 0.0, qy = 0.0, qz = 0.0;
                     bool isfar = false;
+                    const int64_t node = range_node(rl, nr, c0, 64);
                     if (lane < cnt) {
-                        sr = a.src[range_node(rl, nr, c0 + lane)];
+                        sr = a.src[node];
                         qx = sr.yx - ox;
                         qy = sr.yy - oy;
                         qz = sr.yz - oz;
@@ -2195,8 +2213,9 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
                 Src sr;
                 double qx = 0.0, qy = 0.0, qz = 0.0;
                 bool isfar = false;
+                const int64_t node = range_node(rl, nr, c1, 64);
                 if (lane < cnt) {
-                    sr = a.src[range_node(rl, nr, c1 + lane)];
+                    sr = a.src[node];
                     qx = sr.yx - ox;
                     qy = sr.yy - oy;
                     qz = sr.yz - oz;
