@@ -257,3 +257,25 @@ def test_translation_launch_sizes(precision, order):
     for a, w in zip(out[0], out[1]):
         w = w.reshape((40,) + a.shape)
         assert np.abs(w - a[None]).max() <= 1e-13 * np.abs(a).max()
+
+
+@pytest.mark.parametrize("precision,order", [(lss.FP64, 1), (lss.FP64, 2), (lss.FP64, 3), (lss.FP64, 17), (lss.FP64, 40),
+                                             (lss.MIXED, 17), (lss.MIXED, 40)])
+def test_expansion_orders(precision, order):
+    """Expansions evaluated by a wave, from the lowest order (columns of one and two terms) to the highest: the field of
+    the tile loop against that of the fixed tiles (FP64: tile=128, another kernel with the same expansions, 1e-13 of the
+    largest value), and mixed against FP64 at the same order, admissibility, leaf size and cut (2e-6)."""
+    v, t = star_surface(12, seed=9)
+    x = bbox_targets(v, 700, pad=0.1, seed=4)
+    out = []
+    for kw in (dict(precision=lss.FP64, tile=128),
+               dict(precision=precision, tile=0) if precision == lss.FP64 else
+               dict(precision=precision, admissibility=7, leaf_shrink=2.0)):
+        c = lss.Context()
+        c.set_options(far_field=lss.FAR_FMM, fmm_order=order, **kw)
+        c.set_sources(v, t, dunavant6())
+        c.set_sigma(0.5 * triangle_diameters(v, t))
+        out.append(c.eval(x))
+    tol = 1e-13 if precision == lss.FP64 else 2e-6
+    for a, b in zip(*out):
+        assert np.abs(a - b).max() <= tol * np.abs(a).max()
