@@ -894,7 +894,20 @@ __device__ __forceinline__ void stage_local(const FmmEvalArgs &a, int32_t B, dou
 // small tree a target meets as many terms as nodes: 24 ragged surfaces in mixed
 // precision 44.5 -> 42.5 ms, charts of 3e4 triangles in FP64 46.1 -> 43.9, a step
 // of 5e7 targets on 2e6 triangles 375 -> 368.
+//   FUSED: every product goes straight into its sum (12 operations a term in the
+// sums instead of 18, and the doubling of m > 0 taken out of them); for FP64
+// near fields.  Mixed ones keep the order of roundings (see the top of
+// lss_fmm.hip on M2L).  The coefficients are the wave's own, so they are read
+// as scalars, where a read from LDS (8.7 cycles of it for two, three such a
+// term) kept it as busy as the VALU: the two changes 2e6 targets on 2e5
+// triangles 83.7 -> 81.9 ms, charts of 3e4 triangles 43.4 -> 43.1.
 //   MM: 0, 1 or 2 for m = 0, m = 1, m >= 2
+// coefficients of an expansion of one of the wave's boxes, read as scalars
+using Coef = const double __attribute__((address_space(4))) *;
+__device__ __forceinline__ Coef expansion(const double *all, int32_t box, int ncp) {
+    return (Coef)(uint64_t)(all + (int64_t)__builtin_amdgcn_readfirstlane(box) * ncp);
+}
+
 struct ColumnSums {
     double s0, s1, are, aim;        // value, d/dz, and the two parts of dx + i dy
     fmm::cd t, t2;                  // T_j^m or U_j^m of this term and the one before
@@ -902,8 +915,32 @@ struct ColumnSums {
     double re, im;                  // middle coefficient of the row that the next term has met
 };
 
-template <int MM, bool REC, bool S0, bool S1, bool UP>
-__device__ __forceinline__ void m2p_term(ColumnSums &q, const double *M, int j, int m, double w, double rz, double ir2) {
+// value += w Re(t m), and the pairs of the two parts: A += t m (sign +1), A -= conj(t m) (sign -1)
+template <bool FUSED>
+__device__ __forceinline__ void add_value(double &s, double w, const fmm::cd &t, double re, double im) {
+    if (FUSED) {
+        s = fma(t.re, re, s);
+        s = fma(-t.im, im, s);
+    } else {
+        s += w * (t.re * re - t.im * im);
+    }
+}
+template <bool FUSED, bool MINUS>
+__device__ __forceinline__ void add_pair(ColumnSums &q, const fmm::cd &t, double re, double im) {
+    if (FUSED) {
+        q.are = fma(MINUS ? -t.re : t.re, re, q.are);
+        q.are = fma(MINUS ? t.im : -t.im, im, q.are);
+        q.aim = fma(t.re, im, q.aim);
+        q.aim = fma(t.im, re, q.aim);
+    } else {
+        if (MINUS) q.are -= t.re * re - t.im * im;
+        else q.are += t.re * re - t.im * im;
+        q.aim += t.re * im + t.im * re;
+    }
+}
+
+template <bool FUSED, int MM, bool REC, bool S0, bool S1, bool UP>
+__device__ __forceinline__ void m2p_term(ColumnSums &q, Coef M, int j, int m, double w, double rz, double ir2) {
     if (REC) {
         const double a = q.c * rz;
         const fmm::cd tn = {(a * q.t.re - q.b * q.t2.re) * ir2, (a * q.t.im - q.b * q.t2.im) * ir2};
@@ -912,31 +949,23 @@ __device__ __forceinline__ void m2p_term(ColumnSums &q, const double *M, int j, 
         q.b += q.c;
         q.c += 2.0;
     }
-    const double *rj = M + j * j, *rn = M + (j - 1) * (j - 1);
+    Coef rj = M + j * j, rn = M + (j - 1) * (j - 1);
     const fmm::cd t = q.t;
     double re = 0.0, im = 0.0;
     if (S0) {                                      // T_j^m M_j^m
         re = rj[MM ? 2 * m - 1 : 0];
         im = MM ? rj[2 * m] : 0.0;
-        q.s0 += w * (t.re * re - t.im * im);
+        add_value<FUSED>(q.s0, w, t, re, im);
     }
-    if (S1) q.s1 += w * (t.re * q.re - t.im * q.im);       // T_{n+1}^m M_n^m
-    if (UP) {                                      // T_{n+1}^m M_n^{m+1}
-        const double mre = rn[2 * m + 1], mim = rn[2 * m + 2];
-        q.are += t.re * mre - t.im * mim;
-        q.aim += t.re * mim + t.im * mre;
-    }
-    if (MM) {                                      // -conj(T_{n+1}^m M_n^{m-1})
-        const double mre = rn[MM == 1 ? 0 : 2 * m - 3], mim = MM == 1 ? 0.0 : rn[2 * m - 2];
-        q.are -= t.re * mre - t.im * mim;
-        q.aim += t.re * mim + t.im * mre;
-    }
+    if (S1) add_value<FUSED>(q.s1, w, t, q.re, q.im);                                   // T_{n+1}^m M_n^m
+    if (UP) add_pair<FUSED, false>(q, t, rn[2 * m + 1], rn[2 * m + 2]);                 // T_{n+1}^m M_n^{m+1}
+    if (MM) add_pair<FUSED, true>(q, t, rn[MM == 1 ? 0 : 2 * m - 3], MM == 1 ? 0.0 : rn[2 * m - 2]);   // -conj(T_{n+1}^m M_n^{m-1})
     q.re = re;
     q.im = im;
 }
 
-template <int MM>
-__device__ __forceinline__ void m2p_column(ColumnSums &q, const double *M, int m, int p, double rz, double ir2) {
+template <bool FUSED, int MM>
+__device__ __forceinline__ void m2p_column(ColumnSums &q, Coef M, int m, int p, double rz, double ir2) {
     const double w = MM == 0 ? 1.0 : 2.0;
     q.t2 = fmm::cd{0.0, 0.0};
     q.c = 2.0 * m + 1.0;
@@ -944,24 +973,31 @@ __device__ __forceinline__ void m2p_column(ColumnSums &q, const double *M, int m
     if (MM == 0) {                                 // j = 0 meets no row above
         q.re = M[0];
         q.im = 0.0;
-        q.s0 += w * (q.t.re * q.re - q.t.im * q.im);
+        add_value<FUSED>(q.s0, w, q.t, q.re, q.im);
     } else if (m <= p) {
-        m2p_term<MM, false, true, false, false>(q, M, m, m, w, rz, ir2);
+        m2p_term<FUSED, MM, false, true, false, false>(q, M, m, m, w, rz, ir2);
     } else {
-        m2p_term<MM, false, false, false, false>(q, M, m, m, w, rz, ir2);
+        m2p_term<FUSED, MM, false, false, false, false>(q, M, m, m, w, rz, ir2);
         return;
     }
     if (m == p) {
-        m2p_term<MM, true, false, true, false>(q, M, p + 1, m, w, rz, ir2);
+        m2p_term<FUSED, MM, true, false, true, false>(q, M, p + 1, m, w, rz, ir2);
         return;
     }
-    m2p_term<MM, true, true, true, false>(q, M, m + 1, m, w, rz, ir2);
+    m2p_term<FUSED, MM, true, true, true, false>(q, M, m + 1, m, w, rz, ir2);
 #pragma unroll 2
-    for (int j = m + 2; j <= p; ++j) m2p_term<MM, true, true, true, true>(q, M, j, m, w, rz, ir2);
-    m2p_term<MM, true, false, true, true>(q, M, p + 1, m, w, rz, ir2);
+    for (int j = m + 2; j <= p; ++j) m2p_term<FUSED, MM, true, true, true, true>(q, M, j, m, w, rz, ir2);
+    m2p_term<FUSED, MM, true, false, true, true>(q, M, p + 1, m, w, rz, ir2);
 }
 
-__device__ __forceinline__ void wave_m2p_sums(const double *M, double rx, double ry, double rz, int p, double s[4]) {
+// FUSED: the sums of m > 0 count twice, taken out of them by halving those of m = 0
+__device__ __forceinline__ void scale_values(ColumnSums &q, double f) {
+    q.s0 *= f;
+    q.s1 *= f;
+}
+
+template <bool FUSED>
+__device__ __forceinline__ void wave_m2p_sums(Coef M, double rx, double ry, double rz, int p, double s[4]) {
     const double r2 = rx * rx + ry * ry + rz * rz, ir2 = 1.0 / r2;
     ColumnSums q;
     q.s0 = q.s1 = q.are = q.aim = 0.0;
@@ -969,18 +1005,20 @@ __device__ __forceinline__ void wave_m2p_sums(const double *M, double rx, double
     for (int m = 0; m <= p + 1; ++m) {
         if (m > 0) diag = fmm::cscale(fmm::cmul(diag, fmm::cd{rx, ry}), -(2.0 * m - 1.0) * ir2);
         q.t = diag;
-        if (m == 0) m2p_column<0>(q, M, m, p, rz, ir2);
-        else if (m == 1) m2p_column<1>(q, M, m, p, rz, ir2);
-        else m2p_column<2>(q, M, m, p, rz, ir2);
+        if (m == 0) m2p_column<FUSED, 0>(q, M, m, p, rz, ir2);
+        else if (m == 1) m2p_column<FUSED, 1>(q, M, m, p, rz, ir2);
+        else m2p_column<FUSED, 2>(q, M, m, p, rz, ir2);
+        if (FUSED && m == 0) scale_values(q, 0.5);
     }
+    if (FUSED) scale_values(q, 2.0);
     s[0] = q.s0;
     s[1] = q.are;
     s[2] = q.aim;
     s[3] = q.s1;
 }
 
-template <int MM, bool REC, bool LAST>
-__device__ __forceinline__ void l2p_term(ColumnSums &q, const double *L, int j, int m, double w, double rz, double r2,
+template <bool FUSED, int MM, bool REC, bool LAST>
+__device__ __forceinline__ void l2p_term(ColumnSums &q, Coef L, int j, int m, double w, double rz, double r2,
                                          double inv) {
     if (REC) {
         const double a = q.c * rz;
@@ -990,20 +1028,15 @@ __device__ __forceinline__ void l2p_term(ColumnSums &q, const double *L, int j, 
         q.c += 2.0;
     }
     const fmm::cd u = q.t;
-    q.s0 += w * (q.re * u.re - q.im * u.im);
+    add_value<FUSED>(q.s0, w, u, q.re, q.im);
     if (LAST) return;
-    const double *r = L + (j + 1) * (j + 1);
+    Coef r = L + (j + 1) * (j + 1);
     q.re = r[MM ? 2 * m - 1 : 0];
     q.im = MM ? r[2 * m] : 0.0;
-    q.s1 += w * (q.re * u.re - q.im * u.im);
-    const double are = MM == 0 ? -r[1] : r[MM == 1 ? 0 : 2 * m - 3], aim = MM == 0 ? r[2] : MM == 1 ? 0.0 : r[2 * m - 2];
-    q.are += are * u.re - aim * u.im;              // L_{j+1}^{m-1}; L^{-1} = -conj(L^1)
-    q.aim += are * u.im + aim * u.re;
-    if (MM) {                                      // - conj(L_{j+1}^{m+1} U_j^m)
-        const double bre = r[2 * m + 1], bim = r[2 * m + 2];
-        q.are -= bre * u.re - bim * u.im;
-        q.aim += bre * u.im + bim * u.re;
-    }
+    add_value<FUSED>(q.s1, w, u, q.re, q.im);
+    if (MM == 0) add_pair<FUSED, false>(q, u, -r[1], r[2]);                             // L_{j+1}^{-1} = -conj(L_{j+1}^1)
+    else add_pair<FUSED, false>(q, u, r[MM == 1 ? 0 : 2 * m - 3], MM == 1 ? 0.0 : r[2 * m - 2]);   // L_{j+1}^{m-1}
+    if (MM) add_pair<FUSED, true>(q, u, r[2 * m + 1], r[2 * m + 2]);                    // - conj(L_{j+1}^{m+1} U_j^m)
 }
 
 // lane i of v, the same for every lane
@@ -1011,8 +1044,8 @@ __device__ __forceinline__ double lane_value(double v, int i) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i), __builtin_amdgcn_readlane(__double2loint(v), i));
 }
 
-template <int MM>
-__device__ __forceinline__ void l2p_column(ColumnSums &q, const double *L, int m, int p, double rz, double r2) {
+template <bool FUSED, int MM>
+__device__ __forceinline__ void l2p_column(ColumnSums &q, Coef L, int m, int p, double rz, double r2) {
     const double w = MM == 0 ? 1.0 : 2.0;
     const int jl = m + 1 + (threadIdx.x & 63);     // lane i: the quotient of term j = m + 1 + i
     const double invs = 1.0 / (double)((jl + m) * (jl - m));
@@ -1021,16 +1054,17 @@ __device__ __forceinline__ void l2p_column(ColumnSums &q, const double *L, int m
     q.re = L[MM ? m * m + 2 * m - 1 : 0];
     q.im = MM ? L[m * m + 2 * m] : 0.0;
     if (m == p) {
-        l2p_term<MM, false, true>(q, L, m, m, w, rz, r2, 0.0);
+        l2p_term<FUSED, MM, false, true>(q, L, m, m, w, rz, r2, 0.0);
         return;
     }
-    l2p_term<MM, false, false>(q, L, m, m, w, rz, r2, 0.0);
+    l2p_term<FUSED, MM, false, false>(q, L, m, m, w, rz, r2, 0.0);
 #pragma unroll 2
-    for (int j = m + 1; j < p; ++j) l2p_term<MM, true, false>(q, L, j, m, w, rz, r2, lane_value(invs, j - m - 1));
-    l2p_term<MM, true, true>(q, L, p, m, w, rz, r2, lane_value(invs, p - m - 1));
+    for (int j = m + 1; j < p; ++j) l2p_term<FUSED, MM, true, false>(q, L, j, m, w, rz, r2, lane_value(invs, j - m - 1));
+    l2p_term<FUSED, MM, true, true>(q, L, p, m, w, rz, r2, lane_value(invs, p - m - 1));
 }
 
-__device__ __forceinline__ void wave_l2p_sums(const double *L, double rx, double ry, double rz, int p, double s[4]) {
+template <bool FUSED>
+__device__ __forceinline__ void wave_l2p_sums(Coef L, double rx, double ry, double rz, int p, double s[4]) {
     const double r2 = rx * rx + ry * ry + rz * rz;
     ColumnSums q;
     q.s0 = q.s1 = q.are = q.aim = 0.0;
@@ -1038,10 +1072,12 @@ __device__ __forceinline__ void wave_l2p_sums(const double *L, double rx, double
     for (int m = 0; m <= p; ++m) {
         if (m > 0) diag = fmm::cscale(fmm::cmul(diag, fmm::cd{rx, ry}), -0.5 / (double)m);
         q.t = diag;
-        if (m == 0) l2p_column<0>(q, L, m, p, rz, r2);
-        else if (m == 1) l2p_column<1>(q, L, m, p, rz, r2);
-        else l2p_column<2>(q, L, m, p, rz, r2);
+        if (m == 0) l2p_column<FUSED, 0>(q, L, m, p, rz, r2);
+        else if (m == 1) l2p_column<FUSED, 1>(q, L, m, p, rz, r2);
+        else l2p_column<FUSED, 2>(q, L, m, p, rz, r2);
+        if (FUSED && m == 0) scale_values(q, 0.5);
     }
+    if (FUSED) scale_values(q, 2.0);
     s[0] = q.s0;
     s[1] = q.are;
     s[2] = q.aim;
@@ -1049,20 +1085,22 @@ __device__ __forceinline__ void wave_l2p_sums(const double *L, double rx, double
 }
 
 // as fmm::m2p and fmm::l2p
-__device__ __forceinline__ void wave_m2p(const double *M, double rx, double ry, double rz, double inv_s, int p, double &phi,
+template <bool FUSED>
+__device__ __forceinline__ void wave_m2p(Coef M, double rx, double ry, double rz, double inv_s, int p, double &phi,
                                          double g[3]) {
     double s[4];
-    wave_m2p_sums(M, rx, ry, rz, p, s);
+    wave_m2p_sums<FUSED>(M, rx, ry, rz, p, s);
     const double is2 = inv_s * inv_s;
     phi = s[0] * inv_s;
     g[0] = -s[1] * is2;
     g[1] = s[2] * is2;
     g[2] = -s[3] * is2;
 }
-__device__ __forceinline__ void wave_l2p(const double *L, double rx, double ry, double rz, double inv_s, int p, double &phi,
+template <bool FUSED>
+__device__ __forceinline__ void wave_l2p(Coef L, double rx, double ry, double rz, double inv_s, int p, double &phi,
                                          double g[3]) {
     double s[4];
-    wave_l2p_sums(L, rx, ry, rz, p, s);
+    wave_l2p_sums<FUSED>(L, rx, ry, rz, p, s);
     phi = s[0];
     g[0] = s[1] * inv_s;
     g[1] = s[2] * inv_s;
@@ -1078,7 +1116,7 @@ __device__ __forceinline__ void fmm_l2p(const FmmEvalArgs &a, int32_t B, const d
     const double cx = o[0] + (a.ijk[3 * B] + 0.5) * s, cy = o[1] + (a.ijk[3 * B + 1] + 0.5) * s,
                  cz = o[2] + (a.ijk[3 * B + 2] + 0.5) * s;
     const double inv = 1.0 / s;
-    if (WAVE) wave_l2p(Ls, (x - cx) * inv, (y - cy) * inv, (z - cz) * inv, inv, a.p, ph, g);
+    if (WAVE) wave_l2p<false>(expansion(a.L, B, a.ncp), (x - cx) * inv, (y - cy) * inv, (z - cz) * inv, inv, a.p, ph, g);
     else fmm::l2p(Ls, (x - cx) * inv, (y - cy) * inv, (z - cz) * inv, inv, a.p, ph, g);
 }
 
@@ -1697,7 +1735,8 @@ __device__ __forceinline__ void for_tiles(const FmmEvalArgs &a, int *slot, F til
 }
 
 // Static LDS per wave of such a kernel, and the waves of a workgroup whose
-// staging regions (rings, then one expansion, then totals) fit 64 KiB
+// staging regions (rings, then an expansion where one is staged, then totals)
+// fit 64 KiB
 struct WaveLds {
     RangeList rl;
     double box[7];
@@ -1832,24 +1871,22 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
                 nf = nf > kRun64 ? nf - kRun64 : 0;
             }
         }
-        // expansions, one at a time in the wave's region: its share of the M2P
-        // list, and for the last wave the local expansion
+        // expansions: the wave's share of the M2P list, and for the last wave the
+        // local expansion
         double ph = 0.0, g[3] = {0.0, 0.0, 0.0};
         const int m1 = a.m2p_end[B];
         for (int e = a.m2p_beg[B] + w; e < m1; e += W) {
             const int32_t S = a.m2p_src[e];
-            wave_stage(a.M + (int64_t)S * a.ncp, a.ncp, region);
             double r[3], inv, p1, g1[3];
             box_position(a, S, x, y, z, r, inv);
-            wave_m2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
+            wave_m2p<true>(expansion(a.M, S, a.ncp), r[0], r[1], r[2], inv, a.p, p1, g1);
             ph += p1;
             for (int c = 0; c < 3; ++c) g[c] += g1[c];
         }
         if (w == W - 1) {
-            wave_stage(a.L + (int64_t)B * a.ncp, a.ncp, region);
             double r[3], inv, p1, g1[3];
             box_position(a, B, x, y, z, r, inv);
-            wave_l2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
+            wave_l2p<true>(expansion(a.L, B, a.ncp), r[0], r[1], r[2], inv, a.p, p1, g1);
             ph += p1;
             for (int c = 0; c < 3; ++c) g[c] += g1[c];
         }
@@ -1978,10 +2015,10 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
             double r[3], inv, p1, g1[3], h1[6];
             box_position(a, S, x, y, z, r, inv);
             if (local) {
-                wave_l2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
+                wave_l2p<true>(expansion(a.L, B, a.ncp), r[0], r[1], r[2], inv, a.p, p1, g1);
                 fmm::l2p_hess(region, r[0], r[1], r[2], inv, a.p, h1);
             } else {
-                wave_m2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
+                wave_m2p<true>(expansion(a.M, S, a.ncp), r[0], r[1], r[2], inv, a.p, p1, g1);
                 fmm::m2p_hess(region, r[0], r[1], r[2], inv, a.p, h1);
             }
             A.f += p1;
@@ -2100,11 +2137,10 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
         for (int e = a.m2p_beg[B] + w; e < m1 + (w == W - 1 ? W : 0); e += W) {
             const bool local = e >= m1;     // once, for the last wave: the leaf's local expansion
             const int32_t S = local ? B : a.m2p_src[e];
-            wave_stage((local ? a.L : a.M) + (int64_t)S * a.ncp, a.ncp, region);
             double r[3], inv, p1, g1[3];
             box_position(a, S, x, y, z, r, inv);
-            if (local) wave_l2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
-            else wave_m2p(region, r[0], r[1], r[2], inv, a.p, p1, g1);
+            if (local) wave_l2p<true>(expansion(a.L, B, a.ncp), r[0], r[1], r[2], inv, a.p, p1, g1);
+            else wave_m2p<true>(expansion(a.M, S, a.ncp), r[0], r[1], r[2], inv, a.p, p1, g1);
             ph += p1;
             for (int c = 0; c < 3; ++c) g[c] += g1[c];
             if (local) break;
@@ -2136,8 +2172,8 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
 // general loop (float-float offsets, the rational fit for node groups with a
 // pair inside the cut).  Each ring is drained in runs of kRun records, one
 // compensated partial sum per run; the remainders are padded to whole node
-// groups at the end of the tile.  The rings share the LDS with the expansions,
-// which are staged once the pairs are done.
+// groups at the end of the tile.  The expansions follow once the pairs
+// are done.
 //   One wave (light tiles): stages 64 nodes at a time into rings of its own.
 //   A workgroup (heavy tiles): the same results bit for bit, whichever way a
 // tile is taken.  The waves stage kWide chunks of 64 nodes at a time into
@@ -2316,18 +2352,15 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
             }
             const double X = a.tx[ti], Y = a.ty[ti], Z = a.tz[ti];
             double ph = 0.0, g[3] = {0.0, 0.0, 0.0}, mph = 0.0, mg[3] = {0.0, 0.0, 0.0};
-            double *buf = reinterpret_cast<double *>(ring_n);       // the rings are done with
             for (int e = a.m2p_beg[B]; e < a.m2p_end[B]; ++e) {
                 const int32_t S = a.m2p_src[e];
-                wave_stage(a.M + (int64_t)S * a.ncp, a.ncp, buf);
                 double r[3], inv, p1, g1[3];
                 box_position(a, S, X, Y, Z, r, inv);
-                wave_m2p(buf, r[0], r[1], r[2], inv, a.p, p1, g1);
+                wave_m2p<false>(expansion(a.M, S, a.ncp), r[0], r[1], r[2], inv, a.p, p1, g1);
                 mph += p1;
                 for (int c = 0; c < 3; ++c) mg[c] += g1[c];
             }
-            wave_stage(a.L + (int64_t)B * a.ncp, a.ncp, buf);
-            fmm_l2p<true>(a, B, buf, X, Y, Z, ph, g);
+            fmm_l2p<true>(a, B, nullptr, X, Y, Z, ph, g);
             ph += mph;
             g[0] += mg[0];
             g[1] += mg[1];
@@ -2482,7 +2515,7 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
         // product and sum in one rounding as where one wave takes the tile (the
         // compiler contracts them there)
         const double X = a.tx[ti], Y = a.ty[ti], Z = a.tz[ti];
-        double *res = Ls, *buf = Ls + nexp * 256 + w * a.ncp;      // [wave][sum][lane], then the buffers
+        double *res = Ls;                   // [wave][sum][lane]
         double lv[4] = {0.0, 0.0, 0.0, 0.0}, mv[4] = {0.0, 0.0, 0.0, 0.0}, linv = 0.0;
         const int m0 = a.m2p_beg[B], entries = 1 + a.m2p_end[B] - m0;
         for (int k0 = 0; k0 < entries; k0 += nexp) {
@@ -2490,11 +2523,10 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
             __syncthreads();                // the rings, or the results folded last, are done with
             if (w < nexp && k < entries) {
                 const int32_t S = k == 0 ? B : a.m2p_src[m0 + k - 1];
-                wave_stage((k == 0 ? a.L : a.M) + (int64_t)S * a.ncp, a.ncp, buf);
                 double r[3], inv, sums[4];
                 box_position(a, S, X, Y, Z, r, inv);
-                if (k == 0) wave_l2p_sums(buf, r[0], r[1], r[2], a.p, sums);
-                else wave_m2p_sums(buf, r[0], r[1], r[2], a.p, sums);
+                if (k == 0) wave_l2p_sums<false>(expansion(a.L, B, a.ncp), r[0], r[1], r[2], a.p, sums);
+                else wave_m2p_sums<false>(expansion(a.M, S, a.ncp), r[0], r[1], r[2], a.p, sums);
                 for (int c = 0; c < 4; ++c) res[w * 256 + 64 * c + lane] = sums[c];
                 if (lane == 0) scale[w] = inv;
             }
@@ -2579,8 +2611,8 @@ void launch_hess_tile(Ctx &c, unsigned grid, const FmmEvalArgs &a, double *hess)
 // nexp: expansions of a heavy tile evaluated at once (their buffers and
 // results fit the rings' LDS)
 void launch_mixed_waves(Ctx &c, int64_t max_tiles, const FmmEvalArgs &a) {
-    const size_t region = region_for(std::max(kMixedRingBytes, (kMixedWideBytes + kWide - 1) / kWide), a.ncp);
-    const int nexp = (int)std::min<size_t>(kWide, region * kWide / (sizeof(double) * (256 + (size_t)a.ncp)));
+    const size_t region = region_for(std::max(kMixedRingBytes, (kMixedWideBytes + kWide - 1) / kWide), 0);
+    const int nexp = (int)std::min<size_t>(kWide, region * kWide / (sizeof(double) * 256));
     const unsigned grid = (unsigned)std::min<int64_t>(max_tiles > 0 ? max_tiles : 1, kWideWaves / kWide);
     auto k = c.opt.count_useful ? k_eval_fmm_mixed_waves<true> : k_eval_fmm_mixed_waves<false>;
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * kWide), region * kWide, c.stream, a, (int)(region / sizeof(double)), nexp);
@@ -2589,7 +2621,7 @@ void launch_mixed_waves(Ctx &c, int64_t max_tiles, const FmmEvalArgs &a) {
 
 // persistent workgroups of waves: two of kWide waves fill a CU at 128 VGPRs
 void launch_f64_waves(Ctx &c, int64_t max_tiles, const FmmEvalArgs &a) {
-    const size_t region = region_for(kF64RingBytes, a.ncp);
+    const size_t region = region_for(kF64RingBytes, 0);
     const int W = waves_for(region);
     const unsigned grid = (unsigned)std::min<int64_t>(max_tiles > 0 ? max_tiles : 1, kWideWaves / W);
     auto k = c.opt.count_useful ? k_eval_fmm_f64_waves<true> : k_eval_fmm_f64_waves<false>;
