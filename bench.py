@@ -469,9 +469,7 @@ def main():
         pair inside the cut (the near field the method asks for) plus the
         local-expansion evaluation, 8 (p+1)^2 per target; pairs evaluated
         beyond the cut (whole leaves of the near lists) are not counted."""
-        # the FP64 evaluation with the default 64-target tiles is k_eval_fmm_f64_split
-        kname = ("k_eval_fmm_%s" if far else "k_p2p_direct_%s") % (
-            "mixed" if dt == "f32" else ("f64_split" if far else "f64"))
+        kname = ("k_eval_fmm_%s_waves" if far else "k_p2p_direct_%s") % ("mixed" if dt == "f32" else "f64")
         traffic = measured_traffic(kname, desc)
         if r["pair_kernel_launches"] <= 0 or r["pair_kernel_ms"] <= 0:
             return None

@@ -2555,7 +2555,7 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
                 a.grad[3 * o + 2] = ((double)sz + (double)ez) + fma(lv[3], linv, mv[3]);
             }
         }
-        if (a.pairs) {                      // as k_eval_fmm_mixed; the list counts once per tile
+        if (a.pairs) {                      // as above; the list counts once per tile
             const double wu = COUNT ? wave_sum(valid ? (double)nuse : 0.0) : 0.0;
             if (lane == 0) {
                 if (w == 0) {
