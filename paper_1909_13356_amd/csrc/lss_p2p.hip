@@ -1583,8 +1583,9 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
 // outlasts everything else: on 2e5 graded triangles a dozen of 40 000 tiles
 // hold 1e5 to 4e5 nodes and hundreds of M2P boxes where a usual one has 1e4.
 // FP64 evaluation, before with one wave per tile and after: 77 760 chart nodes
-// 4.1 -> 1.8 ms (floor of the VALU issue 0.9), 4.7e5 chart nodes 26 -> 12.6
-// (9.1), 2e6 targets on 2e5 triangles 117 -> 70 (56).
+// 4.1 -> 1.8 ms, 4.7e5 chart nodes 26 -> 12.6, 2e6 targets on 2e5 triangles
+// 117 -> 70; with what the records, ranges and expansions gained since, 1.6, 9.0
+// and 61.
 
 // LDS between lanes of one wave: orders the accesses, no barrier
 __device__ __forceinline__ void wave_sync() {
@@ -2184,7 +2185,7 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
 // Bound by FP32 VALU issue at four waves per SIMD.  One wave per tile before:
 // 1000 targets on 242 000 nodes 3.4 -> 0.75 ms; a graded surface of 31 212
 // triangles with 1e4 to 2e5 targets 18.8 -> 3.5 ms, 8e5 targets 20.5 -> 6.5 ms;
-// 5e7 targets on 2e6 triangles as before.
+// 5e7 targets on 2e6 triangles as before (345, now 302: records, ranges, expansions).
 constexpr int kRun = 32;                 // records per partial sum
 constexpr int kRing = 96;                // a wave's ring: kRun - 1 left over + 64 staged
 constexpr int kRingW = 64 * kWide + 32;  // a workgroup's: kRun - 1 left over + kWide * 64 staged
