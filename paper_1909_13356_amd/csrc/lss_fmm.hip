@@ -11,8 +11,9 @@
 //     so that the operators split in two halves; one product launch and one
 //     sum launch per block of target boxes, each pair's product in a slot of
 //     its own and the sums in a fixed order.
-//   mixed contexts: one launch per displacement class (one dense operator per
-//     class); inside a launch every destination box appears once.  The
+//   mixed contexts, and lists of 2^31 pairs and more: one launch per
+//     displacement class (one dense operator per class); inside a launch every
+//     destination box appears once.  The
 //     rotated form would change the far field by 1e-16, and a Newton iterate
 //     moved by that makes a few FP32 pair sums of a million nodes round the
 //     other way (up to 7e-9 sigma in a node's h); the mixed projection is
@@ -1299,7 +1300,8 @@ void upward_pass(Ctx &c, int p, int ncp, DBuf &flag, DBuf &ids, DBuf &leaves, DB
     }
 }
 
-// M2L of a mixed context, class by class, into t.L (cleared by upward_pass)
+// M2L class by class, into t.L (cleared before): mixed contexts, and lists
+// longer than the plan holds
 void m2l_classwise(Ctx &c, int p, int ncp) {
     Tree &t = c.tree;
     const int64_t per = (int64_t)ncp * ncp;
@@ -1495,8 +1497,9 @@ void build_fmm(Ctx &c) {
         sort_near_lists(c);
         LSS_HIP(hipEventRecord(c.aux_ev[3], c.aux_stream));
     }
-    if (!m2l_rotated(c)) {
+    if (!m2l_planned(c)) {
         LSS_HIP(hipStreamWaitEvent(c.stream, c.aux_ev[1], 0));
+        if (m2l_rotated(c)) launch_fill_zero(c, t.L.as<double>(), t.nboxes * (int64_t)ncp);   // upward_pass did not
         m2l_classwise(c, p, ncp);
     } else {
         m2l_plan(c);

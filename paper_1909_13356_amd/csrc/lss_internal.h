@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "lss.h"
+#include "split_rules.h"
 
 namespace lss {
 
@@ -404,6 +405,8 @@ inline int fmm_order_for(const Ctx &c) {
 // one plan, wherever the near field is summed in FP64, that is in FP64 contexts
 // and for the target-attached width; by displacement class in mixed contexts.
 inline bool m2l_rotated(const Ctx &c) { return c.opt.precision != LSS_MIXED || c.target_widths; }
+// and whether it takes the plan, once the list is emitted (c.tree.n_m2l)
+inline bool m2l_planned(const Ctx &c) { return m2l_rotated(c) && m2l_plan_holds(c.tree.n_m2l); }
 // the boxes (levels, radii, target cuts), then the interaction lists
 void build_tree_boxes(Ctx &c);
 void build_tree_lists(Ctx &c);     // dual traversal; mixed: the M2L list sorted by class

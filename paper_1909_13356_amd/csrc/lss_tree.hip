@@ -945,7 +945,7 @@ void build_tree_lists(Ctx &c) {
     // the direct and M2P lists are sorted by sort_near_lists (the translations
     // do not need them), the M2L list by m2l_plan where that serves; else it
     // is sorted by class here
-    if (m2l_rotated(c)) return;
+    if (m2l_planned(c)) return;
     t.m2l_key2.ensure(8 * (t.n_m2l + 1)); t.m2l_val2.ensure(4 * (t.n_m2l + 1));
     sort_pairs(c, t.m2l_key.as<uint64_t>(), t.m2l_key2.as<uint64_t>(), t.m2l_val.as<int32_t>(),
                t.m2l_val2.as<int32_t>(), t.n_m2l, 32 + bits_for(kNClass));
