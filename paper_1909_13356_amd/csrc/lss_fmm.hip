@@ -916,6 +916,16 @@ __global__ void k_m2l_rekey(int64_t n, const int32_t *__restrict__ rank, int shi
              (T & ((1u << shift) - 1u));
 }
 
+// the same keys for blocks of 2^to boxes instead of 2^from, to < from
+__global__ void k_m2l_reshift(int64_t n, int from, int to, uint64_t *key, int32_t *word) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *word = (int32_t)n;
+    if (i >= n) return;
+    const uint64_t k = key[i], rank = (k >> from) & ((1u << kRankBits) - 1u);
+    const uint64_t T = (k >> (kRankBits + from) << from) | (k & ((1ull << from) - 1ull));
+    key[i] = ((T >> to) << (kRankBits + to)) | (rank << to) | (T & ((1ull << to) - 1ull));
+}
+
 // Sorted pairs: tile heads (every kPairs-th pair of a (block, group) segment,
 // the segment starting at the first key with its block and its group's lowest
 // rank), the groups in use, the first pair of every block, and the pairs
@@ -1052,7 +1062,13 @@ static_assert((2 * kR + 1) * (2 * kR + 1) <= 256, "the angle index takes 8 bits 
 // and each box's pairs.  A block holds 2^shift target boxes, as many as keep
 // the products of an average block near kM2LBytes: large enough to fill the
 // chip several times over (about 1e5 pairs), small enough that the expansions
-// of a block's sources stay in the caches between its groups.
+// of a block's sources stay in the caches between its groups.  Blocks of a
+// surface's tree differ little (the fullest holds at most 1.2 times the mean's
+// pairs on the graded surfaces measured), but boxes without pairs pull the mean
+// down: where the fullest block would take more than twice kM2LBytes the
+// blocks are halved and the pairs sorted again, until it does not or a block
+// is one box.  (4096 boxes of a volume's triangles beside 36 000 boxes of small
+// meshes, order 26: 8.2 GiB before.)
 constexpr double kM2LBytes = 1024.0 * 1024.0 * 1024.0;
 
 void m2l_plan(Ctx &c) {
@@ -1061,11 +1077,10 @@ void m2l_plan(Ctx &c) {
     if (n == 0) return;
     const M2LClasses &cl = m2l_classes();
     const int p = t.p;
-    const double per_box = (double)n / (double)t.nboxes * 8.0 * (p + 1) * (p + 2);
+    const double pair_bytes = 8.0 * (p + 1) * (p + 2);     // at most: the highest order's rows
+    const double per_box = (double)n / (double)t.nboxes * pair_bytes;
     int shift = 0;
     while ((int64_t(1) << shift) < t.nboxes && 2.0 * per_box * (double)(int64_t(1) << shift) <= kM2LBytes) ++shift;
-    t.m2l_shift = shift;
-    const int nblk = (int)((t.nboxes - 1) >> shift) + 1;
     if (!t.m2l_tab.p) {
         t.m2l_tab.ensure(4 * (2 * kNClass + cl.ngroups));
         LSS_HIP(hipMemcpyAsync(t.m2l_tab.p, cl.rank.data(), 4 * kNClass, hipMemcpyHostToDevice, c.stream));
@@ -1075,23 +1090,11 @@ void m2l_plan(Ctx &c) {
                                hipMemcpyHostToDevice, c.stream));
     }
     const int32_t *rank = t.m2l_tab.as<int32_t>(), *info = rank + kNClass, *grp_rank = info + kNClass;
-    // meta: used flag per group, first pair per block (+ end), first tile per block (+ end), count, tiles
-    const int64_t nmeta = cl.ngroups + 2 * (nblk + 1) + 2;
-    t.m2l_meta.ensure(4 * nmeta);
-    int32_t *used = t.m2l_meta.as<int32_t>(), *blk = used + cl.ngroups, *blk_tile = blk + nblk + 1,
-            *count = blk_tile + nblk + 1, *ntiles = count + 1;
-    LSS_HIP(hipMemsetAsync(used, 0, 4 * cl.ngroups, c.stream));
-    hipLaunchKernelGGL(k_m2l_rekey, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, rank, shift,
-                       t.m2l_key.as<uint64_t>(), count);
     t.m2l_key2.ensure(8 * n);
     t.m2l_val2.ensure(4 * n);
-    int bb = 1;
-    while ((int64_t(1) << bb) < nblk) ++bb;
     // own sort workspace (the near lists are sorted on the other stream meanwhile)
     const size_t stb = sort_pairs_u64_tmp_bytes(n);
     t.m2l_tmp.ensure(stb);
-    sort_pairs_u64(t.m2l_tmp.p, stb, t.m2l_key.as<uint64_t>(), t.m2l_key2.as<uint64_t>(), t.m2l_val.as<int32_t>(),
-                   t.m2l_val2.as<int32_t>(), n, 0, kRankBits + shift + bb, c.stream);
     t.m2l_flag.ensure(4 * n);
     t.m2l_pos.ensure(4 * n);
     t.m2l_ts.ensure(4 * (n + 1));
@@ -1099,36 +1102,61 @@ void m2l_plan(Ctx &c) {
     t.m2l_csr_key2.ensure(8 * n);
     t.m2l_csr.ensure(4 * n);
     t.m2l_csr2.ensure(4 * n);
-    hipLaunchKernelGGL(k_m2l_mark, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, t.m2l_key2.as<uint64_t>(), shift,
-                       nblk, info, grp_rank, t.m2l_flag.as<int32_t>(), t.m2l_pos.as<int32_t>(), used, blk,
-                       t.m2l_csr_key.as<uint64_t>(), t.m2l_csr.as<int32_t>());
-    LSS_CHECK_LAUNCH("k_m2l_mark");
     t.m2l_bsum.ensure(4 * ((size_t)compact_blocks(n) + 2));
-    compact_flags(c, n, count, t.m2l_flag.as<int32_t>(), t.m2l_pos.as<int32_t>(), t.m2l_ts.as<int32_t>(), ntiles,
-                  t.m2l_bsum.as<int32_t>());
-    hipLaunchKernelGGL(k_m2l_blk_tiles, dim3(grid_for(nblk + 1)), dim3(kBlk), 0, c.stream, nblk, blk, ntiles,
-                       (int32_t)n, t.m2l_ts.as<int32_t>(), blk_tile);
-    LSS_CHECK_LAUNCH("k_m2l_blk_tiles");
-    std::vector<int32_t> h(cl.ngroups + 2 * (nblk + 1));
-    LSS_HIP(hipMemcpyAsync(h.data(), used, 4 * h.size(), hipMemcpyDeviceToHost, c.stream));
-    // the pairs of every box, in rank order (the sort is stable)
-    int tb = 1;
-    while ((int64_t(1) << tb) < t.nboxes) ++tb;
-    sort_pairs_u64(t.m2l_tmp.p, stb, t.m2l_csr_key.as<uint64_t>(), t.m2l_csr_key2.as<uint64_t>(),
-                   t.m2l_csr.as<int32_t>(), t.m2l_csr2.as<int32_t>(), n, 0, tb, c.stream);
-    t.m2l_beg.ensure(4 * t.nboxes);
-    t.m2l_end.ensure(4 * t.nboxes);
-    LSS_HIP(hipMemsetAsync(t.m2l_beg.p, 0, 4 * t.nboxes, c.stream));
-    LSS_HIP(hipMemsetAsync(t.m2l_end.p, 0, 4 * t.nboxes, c.stream));
-    hipLaunchKernelGGL(k_m2l_ranges, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, t.m2l_csr_key2.as<uint64_t>(),
-                       t.m2l_beg.as<int32_t>(), t.m2l_end.as<int32_t>());
-    LSS_CHECK_LAUNCH("k_m2l_ranges");
-    LSS_HIP(hipStreamSynchronize(c.stream));
-    t.m2l_used.clear();
-    for (int g = 0; g < cl.ngroups; ++g)
-        if (h[g]) t.m2l_used.push_back(g);
-    t.m2l_blk.assign(h.begin() + cl.ngroups, h.begin() + cl.ngroups + nblk + 1);
-    t.m2l_blk_tile.assign(h.begin() + cl.ngroups + nblk + 1, h.end());
+    for (int from = -1;;) {
+        const int nblk = (int)((t.nboxes - 1) >> shift) + 1;
+        // meta: used flag per group, first pair per block (+ end), first tile per block (+ end), count, tiles
+        const int64_t nmeta = cl.ngroups + 2 * ((int64_t)nblk + 1) + 2;
+        t.m2l_meta.ensure(4 * nmeta);
+        int32_t *used = t.m2l_meta.as<int32_t>(), *blk = used + cl.ngroups, *blk_tile = blk + nblk + 1,
+                *count = blk_tile + nblk + 1, *ntiles = count + 1;
+        LSS_HIP(hipMemsetAsync(used, 0, 4 * cl.ngroups, c.stream));
+        if (from < 0)
+            hipLaunchKernelGGL(k_m2l_rekey, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, rank, shift,
+                               t.m2l_key.as<uint64_t>(), count);
+        else
+            hipLaunchKernelGGL(k_m2l_reshift, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, from, shift,
+                               t.m2l_key.as<uint64_t>(), count);
+        int bb = 1;
+        while ((int64_t(1) << bb) < nblk) ++bb;
+        sort_pairs_u64(t.m2l_tmp.p, stb, t.m2l_key.as<uint64_t>(), t.m2l_key2.as<uint64_t>(), t.m2l_val.as<int32_t>(),
+                       t.m2l_val2.as<int32_t>(), n, 0, kRankBits + shift + bb, c.stream);
+        hipLaunchKernelGGL(k_m2l_mark, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, t.m2l_key2.as<uint64_t>(), shift,
+                           nblk, info, grp_rank, t.m2l_flag.as<int32_t>(), t.m2l_pos.as<int32_t>(), used, blk,
+                           t.m2l_csr_key.as<uint64_t>(), t.m2l_csr.as<int32_t>());
+        LSS_CHECK_LAUNCH("k_m2l_mark");
+        compact_flags(c, n, count, t.m2l_flag.as<int32_t>(), t.m2l_pos.as<int32_t>(), t.m2l_ts.as<int32_t>(), ntiles,
+                      t.m2l_bsum.as<int32_t>());
+        hipLaunchKernelGGL(k_m2l_blk_tiles, dim3(grid_for(nblk + 1)), dim3(kBlk), 0, c.stream, nblk, blk, ntiles,
+                           (int32_t)n, t.m2l_ts.as<int32_t>(), blk_tile);
+        LSS_CHECK_LAUNCH("k_m2l_blk_tiles");
+        std::vector<int32_t> h(cl.ngroups + 2 * ((size_t)nblk + 1));
+        LSS_HIP(hipMemcpyAsync(h.data(), used, 4 * h.size(), hipMemcpyDeviceToHost, c.stream));
+        // the pairs of every box, in rank order (the sort is stable)
+        int tb = 1;
+        while ((int64_t(1) << tb) < t.nboxes) ++tb;
+        sort_pairs_u64(t.m2l_tmp.p, stb, t.m2l_csr_key.as<uint64_t>(), t.m2l_csr_key2.as<uint64_t>(),
+                       t.m2l_csr.as<int32_t>(), t.m2l_csr2.as<int32_t>(), n, 0, tb, c.stream);
+        t.m2l_beg.ensure(4 * t.nboxes);
+        t.m2l_end.ensure(4 * t.nboxes);
+        LSS_HIP(hipMemsetAsync(t.m2l_beg.p, 0, 4 * t.nboxes, c.stream));
+        LSS_HIP(hipMemsetAsync(t.m2l_end.p, 0, 4 * t.nboxes, c.stream));
+        hipLaunchKernelGGL(k_m2l_ranges, dim3(grid_for(n)), dim3(kBlk), 0, c.stream, n, t.m2l_csr_key2.as<uint64_t>(),
+                           t.m2l_beg.as<int32_t>(), t.m2l_end.as<int32_t>());
+        LSS_CHECK_LAUNCH("k_m2l_ranges");
+        LSS_HIP(hipStreamSynchronize(c.stream));
+        t.m2l_shift = shift;
+        t.m2l_used.clear();
+        for (int g = 0; g < cl.ngroups; ++g)
+            if (h[g]) t.m2l_used.push_back(g);
+        t.m2l_blk.assign(h.begin() + cl.ngroups, h.begin() + cl.ngroups + nblk + 1);
+        t.m2l_blk_tile.assign(h.begin() + cl.ngroups + nblk + 1, h.end());
+        int64_t most = 0;
+        for (int b = 0; b < nblk; ++b) most = std::max(most, t.m2l_blk[b + 1] - t.m2l_blk[b]);
+        double over = (double)most * pair_bytes / (2.0 * kM2LBytes);
+        if (over <= 1.0 || shift == 0) return;
+        for (from = shift; over > 1.0 && shift > 0; over *= 0.5) --shift;
+    }
 }
 
 // M2L of every pair: t.L from t.M (written whole), operators of the groups in
@@ -1214,9 +1242,16 @@ void m2l_pass(Ctx &c, int p, int ncp) {
     }
     t.m2l_grp.ensure(4 * t.h_m2l_grp.size());
     LSS_HIP(hipMemcpyAsync(t.m2l_grp.p, t.h_m2l_grp.data(), 4 * t.h_m2l_grp.size(), hipMemcpyHostToDevice, c.stream));
+    // a launch takes a block, or as many as hold kM2LBytes of products together
     const int nblk = (int)t.m2l_blk.size() - 1;
+    const int64_t together = (int64_t)(kM2LBytes / (16.0 * nqmax));
+    std::vector<int> cut{0};
     int64_t most = 0;
-    for (int b = 0; b < nblk; ++b) most = std::max(most, t.m2l_blk[b + 1] - t.m2l_blk[b]);
+    for (int b = 1; b <= nblk; ++b) {
+        if (b < nblk && t.m2l_blk[b + 1] - t.m2l_blk[cut.back()] <= together) continue;
+        most = std::max(most, t.m2l_blk[b] - t.m2l_blk[cut.back()]);
+        cut.push_back(b);
+    }
     t.m2l_y.ensure(sizeof(double2) * (size_t)most * rowmax);
     M2LArgs a;
     a.key = t.m2l_key2.as<uint64_t>();
@@ -1237,15 +1272,16 @@ void m2l_pass(Ctx &c, int p, int ncp) {
     a.Y = t.m2l_y.as<double2>();
     a.ystride = rowmax;
     const Geo g{t.root.as<double>(), t.bmesh.as<int32_t>()};
-    for (int b = 0; b < nblk; ++b) {
-        a.tile0 = t.m2l_blk_tile[b];
-        a.ntiles = t.m2l_blk_tile[b + 1] - a.tile0;
-        a.p0 = t.m2l_blk[b];
+    for (size_t k = 0; k + 1 < cut.size(); ++k) {
+        a.tile0 = t.m2l_blk_tile[cut[k]];
+        a.ntiles = t.m2l_blk_tile[cut[k + 1]] - a.tile0;
+        a.p0 = t.m2l_blk[cut[k]];
         if (a.ntiles > 0) {
             const int64_t wg = ceil_div(a.ntiles, 8 * kXcdTiles) * 8 * kXcdTiles * a.rowtiles;
             hipLaunchKernelGGL(k_m2l, dim3((unsigned)wg), dim3(256), 0, c.stream, a);
         }
-        const int64_t b0 = (int64_t)b << t.m2l_shift, nb = std::min<int64_t>(int64_t(1) << t.m2l_shift, t.nboxes - b0);
+        const int64_t b0 = (int64_t)cut[k] << t.m2l_shift,
+                      nb = std::min<int64_t>((int64_t)cut[k + 1] << t.m2l_shift, t.nboxes) - b0;
         hipLaunchKernelGGL(k_m2l_sum, dim3((unsigned)nb), dim3(256), 0, c.stream, a, b0, t.m2l_beg.as<int32_t>(),
                            t.m2l_end.as<int32_t>(), t.m2l_csr2.as<int32_t>(), nqmax, g, t.level.as<int32_t>(),
                            t.L.as<double>());

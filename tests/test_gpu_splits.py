@@ -279,3 +279,29 @@ def test_expansion_orders(precision, order):
     tol = 1e-13 if precision == lss.FP64 else 2e-6
     for a, b in zip(*out):
         assert np.abs(a - b).max() <= tol * np.abs(a).max()
+
+
+def test_m2l_products_are_bounded():
+    """A volume's triangles beside 4000 meshes whose boxes have no pair: the M2L products of one launch stay within 2 GiB
+    however the pairs are spread over the boxes (the build takes less than 4 GiB in all; 1.4 GiB are expansions, lists
+    and records), and the field equals the direct sum (1e-12)."""
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(3)
+    m = 18_000
+    v = (rng.random((m, 1, 3)) + 0.01 * rng.standard_normal((m, 3, 3))).reshape(-1, 3)
+    t = np.arange(3 * m, dtype=np.int32).reshape(m, 3)
+    cube = cube_mesh(1)
+    small = dict(verts=cube[0], tris=cube[1], sigma=np.full(len(cube[1]), 1e-3), targets=np.zeros((0, 3)))
+    b = configs.concat_batch([dict(verts=v, tris=t, sigma=np.full(m, 1e-3), targets=rng.random((500, 3)))] + [small] * 4000)
+    free = torch.cuda.mem_get_info()[0]
+    c = lss.Context()
+    c.set_options(far_field=lss.FAR_FMM, leaf_capacity=100)
+    c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+    c.set_sigma(b["sigma"])
+    c.build()
+    assert free - torch.cuda.mem_get_info()[0] < 4 << 30
+    assert c.stats()["n_m2l"] > 1_000_000
+    got = c.eval(b["targets"], x_mesh=b["target_mesh"])
+    c.set_options(far_field=lss.FAR_DIRECT)
+    want = c.eval(b["targets"], x_mesh=b["target_mesh"])
+    assert _err(got[0], want[0]) <= 1e-12 and _err(got[1], want[1]) <= 1e-12
