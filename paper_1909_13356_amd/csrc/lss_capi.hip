@@ -233,7 +233,7 @@ void eval_fmm_bufs(Ctx &c, const EvalBufs &b, int64_t n, double *phi, double *gr
     launch_locate_targets(c, n, b.n_dev, b.tx, b.ty, b.tz, b.tmesh, b.key, b.perm);
     sort_pairs_u64(b.sort_tmp, b.sort_bytes, b.key, b.key2, b.perm, b.perm2, n, 0, 64, c.stream);
     build_tiles(c, n, b.n_dev, b.key2, fmm_tile(c), b.tleaf, b.tstart, b.ntiles, b.flag, b.pos, b.blocksum);
-    order_tiles(c, n, b.ntiles, b.tstart, b.tleaf, b.order);
+    order_tiles(c, n, b.ntiles, b.tstart, b.tleaf, b.order, hess || ms);
     if (b.pairs) {
         LSS_HIP(hipMemsetAsync(b.pairs, 0, 4 * sizeof(double), c.stream));
         c.ev_begin();

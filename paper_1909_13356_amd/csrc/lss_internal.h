@@ -437,8 +437,10 @@ constexpr int kCostBuckets = 128;
 constexpr int kWide = 8;                  // most waves of an evaluation workgroup (for_tiles)
 constexpr int kHessWaves = 4;              // and of the Hessian and sigma(x) evaluations
 constexpr int kWideWaves = 4096;          // waves resident on the chip (four per SIMD)
+constexpr int kHessResident = 3072;        // and of these (three per SIMD)
+// hess: the tiles are for the Hessian or the sigma(x) evaluation
 void order_tiles(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const int32_t *tile_start,
-                 const int32_t *leaf, int32_t *order);
+                 const int32_t *leaf, int32_t *order, bool hess = false);
 void build_tiles_unsorted(Ctx &c, int64_t n_max, const int32_t *n_dev, int tile);
 void rebin_active(Ctx &c, int64_t N, int64_t nact);
 

@@ -2599,7 +2599,7 @@ void launch_tile(Ctx &c, int64_t n, const int32_t *n_dev, const double *tx, cons
 // persistent workgroups of the Hessian and sigma(x) kernels: three of
 // kHessWaves waves fill a CU (168 VGPRs)
 unsigned hess_grid(int64_t max_tiles, int W) {
-    return (unsigned)std::min<int64_t>(max_tiles > 0 ? max_tiles : 1, 256 * 12 / W);
+    return (unsigned)std::min<int64_t>(max_tiles > 0 ? max_tiles : 1, kHessResident / W);
 }
 
 template <int TILE>

@@ -593,17 +593,21 @@ __global__ void k_tile_bucket_count(int64_t max_tiles, const int32_t *__restrict
 // single block: offsets from the counts, counts cleared for the next use, and
 // how many of the first (most expensive) tiles are heavy: a whole workgroup
 // takes each of them (for_tiles in lss_p2p.hip).  The line: a cost of at least
-// 1 / share of what each of the chip's resident waves gets, so that the tiles
+// 1 / share of what each of the kernel's resident waves gets, so that the tiles
 // that single waves take end within that part of the launch of each other.
-//   FP64, 8: the waves of a heavy tile are independent, nothing is lost on it.
-// 4e5 targets near a uniform sphere, and on a graded surface (ms): 22.6, 11.8
-// at 8; 22.6, 13.5 at 4; 31.7, 13.8 at 2 (one wave per tile: 25.5, 48.0).
-//   Mixed, 1.4: a heavy tile's waves work in step, 15% slower than single
+//   Independent waves, 8 (FP64 evaluation; Hessian and sigma(x), which sum in
+// FP64 in mixed contexts too): nothing is lost on a heavy tile.  FP64
+// evaluation of 4e5 targets near a uniform sphere, and on a graded surface (ms):
+// 22.6, 11.8 at 8; 22.6, 13.5 at 4; 31.7, 13.8 at 2 (one wave per tile: 25.5,
+// 48.0).  Hessian at 2.9e5 chart nodes of 6348 triangles in an FP64 and in a
+// mixed context, sigma(x) at 1e5 targets on 43 200 triangles in a mixed one:
+// 11.0, 7.7, 3.4 at 8; 11.0, 7.7, 3.7 at 4; 13.8, 9.0, 3.9 at 1.4.
+//   Waves in step, 1.4 (mixed evaluation): a heavy tile is 15% slower than single
 // waves where the chip is full anyway.  3e5 targets near the sphere, 8e5 on the
 // graded surface (ms): 6.9, 6.9 at 1.4; 6.7, 7.1 at 1; 7.9, 6.5 at 2 (one wave
 // per tile: 7.4, 21.2).
-constexpr double kHeavyShare64 = 8.0, kHeavyShareMixed = 1.4;
-__global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket, double share) {
+constexpr double kShareApart = 8.0, kShareInStep = 1.4;
+__global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket, double line) {
     constexpr int kPer = kCostBuckets / 64;
     const int lane = threadIdx.x;
     int32_t n[kPer], s = 0;
@@ -628,7 +632,7 @@ __global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket, double
         const int i = kPer * lane + k;
         bucket[kCostBuckets + i] = at;
         at += n[k];
-        if (bucket_cost(i) * kWideWaves * share >= total) {
+        if (bucket_cost(i) * line >= total) {
             heavy = at;
             hc += n[k] * bucket_cost(i);
         }
@@ -1039,13 +1043,14 @@ int64_t build_tiles(Ctx &c, int64_t n_max, const int32_t *n_dev, const uint64_t 
 // No sort, no host synchronisation, no allocation: safe under stream capture
 // once the buffers have been sized by ensure_tiles.
 void order_tiles(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const int32_t *tile_start,
-                 const int32_t *leaf, int32_t *order) {
+                 const int32_t *leaf, int32_t *order, bool hess) {
     Tree &t = c.tree;
     const unsigned g = grid_for(max_tiles) < 2048u ? grid_for(max_tiles) : 2048u;
     hipLaunchKernelGGL(k_tile_bucket_count, dim3(g), dim3(kBlk), 0, c.stream, max_tiles, ntiles_dev, tile_start, leaf,
                        t.near_cnt.as<int64_t>(), c.tile_bucket.as<int32_t>());
     hipLaunchKernelGGL(k_tile_bucket_scan, dim3(1), dim3(64), 0, c.stream, c.tile_bucket.as<int32_t>(),
-                       c.opt.precision == LSS_MIXED ? kHeavyShareMixed : kHeavyShare64);
+                       hess ? kShareApart * kHessResident
+                            : (c.opt.precision == LSS_MIXED ? kShareInStep : kShareApart) * kWideWaves);
     hipLaunchKernelGGL(k_tile_bucket_scatter, dim3(g), dim3(kBlk), 0, c.stream, max_tiles, ntiles_dev, tile_start,
                        leaf, t.near_cnt.as<int64_t>(), c.tile_bucket.as<int32_t>(), order);
     LSS_CHECK_LAUNCH("order_tiles");

@@ -305,3 +305,19 @@ def test_m2l_products_are_bounded():
     c.set_options(far_field=lss.FAR_DIRECT)
     want = c.eval(b["targets"], x_mesh=b["target_mesh"])
     assert _err(got[0], want[0]) <= 1e-12 and _err(got[1], want[1]) <= 1e-12
+
+
+def test_multiscale_is_the_same_in_both_precisions():
+    """The target-attached width is summed in FP64 in either precision: with the same tree the same bits.  At 60 000
+    targets some tiles are shared by a workgroup's waves, which add their totals, and most are not; which ones must not
+    depend on the context's precision."""
+    v, t = star_surface(24, seed=8)
+    x = bbox_targets(v, 60_000, pad=0.1, seed=5)
+    out = []
+    for prec in (lss.FP64, lss.MIXED):
+        c = lss.Context()
+        c.set_options(precision=prec, far_field=lss.FAR_FMM, fmm_order=18, cut_factor=7.0, leaf_capacity=64,
+                      leaf_shrink=2.0, admissibility=5, sigma_interp=1)
+        c.set_sources(v, t, dunavant6())
+        out.append(c.eval_multiscale(x, 2.5, 0.0))
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
