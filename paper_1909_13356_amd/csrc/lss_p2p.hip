@@ -560,16 +560,11 @@ __device__ __forceinline__ double wave_sum(double v) {
 // k_direct_fold adds the pieces of a target in order by two-sum, so the sums
 // do not depend on which workgroup ran first.  Chunks and runs are those of
 // the unsplit loop: the pair arithmetic is the same bit for bit.  FP64, 4096
-// targets on 36 864 nodes: 7.59 -> 0.47 ms a call (16 workgroups, each a
-// serial chain of 144 chunks, before; 2048 now).
+// targets on 36 864 nodes: 7.59 -> 0.45 ms a call (16 workgroups, each a
+// serial chain of 144 chunks, before; 1152 of two chunks now).
 template <int TILE>
 __device__ __forceinline__ void split_range(int64_t &lo, int64_t &hi) {
-    if (gridDim.y == 1) return;
-    const int64_t chunks = (hi - lo + TILE - 1) / TILE;
-    const int64_t per = (chunks + gridDim.y - 1) / gridDim.y * TILE;
-    const int64_t a = lo + (int64_t)blockIdx.y * per;
-    lo = a < hi ? a : hi;
-    hi = lo + per < hi ? lo + per : hi;
+    if (gridDim.y > 1) piece_range(TILE, blockIdx.y, gridDim.y, lo, hi);
 }
 
 template <class T>
@@ -2752,19 +2747,10 @@ void launch_eval_fmm(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const
     LSS_CHECK_LAUNCH("k_eval_outside");
 }
 
-// Pieces of the node range for a direct sum of n targets.  1024 tiles of 256
-// targets fill the 256 CUs four deep; below 640 the last round of workgroups
-// leaves CUs idle (600 tiles: up to 3 on a CU where the average is 2.3), so
-// the nodes are split until up to 2048 workgroups run.  A piece holds at least
-// one chunk.  n times the pieces stays below 2^19, so the partial sums (64
-// bytes per target and piece) and the buffers of n targets fit the 48 MiB of
-// the allocation-free entry point at every n.
 int direct_splits(const Ctx &c, int64_t n) {
     const int tile = direct_tile(c);
-    const int64_t tiles = ceil_div(n > 0 ? n : 1, tile), chunks = ceil_div(c.nnodes > 0 ? c.nnodes : 1, tile);
-    const int64_t full = (int64_t)2048 * (256 / tile);
-    if (tiles >= full * 5 / 16) return 1;
-    return (int)std::min(std::min(full / tiles, chunks), (int64_t)1024);
+    return direct_pieces(ceil_div(n > 0 ? n : 1, tile), ceil_div(c.nnodes > 0 ? c.nnodes : 1, tile), tile,
+                         c.nmesh == 1);
 }
 
 size_t direct_part_bytes(const Ctx &c, int64_t n) {

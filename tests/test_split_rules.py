@@ -21,3 +21,30 @@ def test_m2l_plan_ends_where_its_indices_do(tmp_path):
         for (int64_t n : {int64_t(0), int64_t(1), (int64_t(1) << 31) - 1, int64_t(1) << 31, int64_t(1) << 40})
             printf("%d ", m2l_plan_holds(n));
     """) == ["1", "1", "1", "0", "0"]
+
+
+def test_every_piece_of_a_direct_sum_has_work(tmp_path):
+    """All tile widths, target and node counts up to where the split ends: the pieces cover the nodes in order, none is
+    empty where a tile walks all nodes, and targets times pieces stay below 2^19 (the workspace of the allocation-free
+    call)."""
+    assert _run(tmp_path, """
+        for (int tile : {64, 128, 256})
+            for (int64_t n = 1; n < 200000; n += 1 + n / 7)
+                for (int64_t nodes = 1; nodes < 3000000; nodes += 1 + nodes / 9)
+                    for (bool whole : {true, false}) {
+                        const int64_t tiles = (n + tile - 1) / tile, chunks = (nodes + tile - 1) / tile;
+                        const int s = direct_pieces(tiles, chunks, tile, whole);
+                        int64_t at = 0, none = 0;
+                        for (int k = 0; k < s; ++k) {
+                            int64_t lo = 0, hi = nodes;
+                            piece_range(tile, k, s, lo, hi);
+                            if (lo != at || hi < lo || (whole && hi == lo)) ++none;
+                            at = hi;
+                        }
+                        if (none || at != nodes || s < 1 || (s > 1 && n * s > (1 << 19))) {
+                            printf("%d %ld %ld: %d pieces, %ld wrong ", tile, (long)n, (long)nodes, s, (long)none);
+                            return 0;
+                        }
+                    }
+        printf("ok");
+    """) == ["ok"]
