@@ -212,6 +212,7 @@ constexpr int kInterpWaves = 16;                     // waves of a workgroup, at
 constexpr int64_t kInterpRegion = 24 * 1024;         // node values that a wave stages, bytes, at most
 constexpr int kInterpLoads = 12;                     // of them on their way at once
 constexpr int64_t kInterpLds = 160 * 1024;
+constexpr size_t kMatrixKept = (size_t)64 << 20;     // matrix buffer that the context keeps between calls, at most
 
 // Same product on the FP64 matrix cores: rows are the points, columns the
 // (triangle, component) pairs, the nodes are contracted.  A wave takes T
@@ -442,6 +443,7 @@ void chart_interp(Ctx &c, const double *chart_uv, int32_t np, const double *f, i
     int32_t bad = 0;
     LSS_HIP(hipMemcpyAsync(&bad, dbad, sizeof(bad), hipMemcpyDeviceToHost, c.stream));
     LSS_HIP(hipStreamSynchronize(c.stream));                // the temporaries are freed on return
+    if (c.interp_mat.bytes > kMatrixKept) c.interp_mat.release();
     if (bad) throw Error{LSS_EINVAL, kNotUnisolvent};
     if (!dev) LSS_HIP(hipMemcpy(out, po, sizeof(double) * nout, hipMemcpyDeviceToHost));
 }

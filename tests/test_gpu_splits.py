@@ -321,3 +321,20 @@ def test_multiscale_is_the_same_in_both_precisions():
         c.set_sources(v, t, dunavant6())
         out.append(c.eval_multiscale(x, 2.5, 0.0))
     assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+def test_chart_interp_gives_a_large_matrix_back():
+    """The matrix to 2^20 points (0.4 GB) is not held by the context after the call: less than 128 MiB stay (64 MiB at
+    most of it), and the values are those of a call with few of the points (1e-12)."""
+    torch = pytest.importorskip("torch")
+    v, t = cube_mesh(1)
+    uv, rng = chart_nodes(8), np.random.default_rng(4)
+    ev = rng.dirichlet([1, 1, 1], 1 << 20)[:, :2]
+    f = rng.standard_normal(len(t) * len(uv))
+    c = lss.Context()
+    c.set_sources(v, t, dunavant6())
+    few = c.chart_interp(uv, f, ev[:: 1 << 10]).reshape(len(t), -1)
+    free = torch.cuda.mem_get_info()[0]
+    got = c.chart_interp(uv, f, ev).reshape(len(t), -1)
+    assert free - torch.cuda.mem_get_info()[0] < 128 << 20
+    assert np.abs(got[:, :: 1 << 10] - few).max() <= 1e-12 * np.abs(few).max()
