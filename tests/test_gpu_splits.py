@@ -338,3 +338,22 @@ def test_chart_interp_gives_a_large_matrix_back():
     got = c.chart_interp(uv, f, ev).reshape(len(t), -1)
     assert free - torch.cuda.mem_get_info()[0] < 128 << 20
     assert np.abs(got[:, :: 1 << 10] - few).max() <= 1e-12 * np.abs(few).max()
+
+
+def test_sigma_field_pieces_of_several_runs():
+    """1e5 points and 76 runs of 256 centroids, split in five: pieces of several runs, a short last one, and in the
+    second mesh (eleven runs, the first shared with the other mesh) one without any.  A point's nearest centroid lies in
+    one of them, so the merge rescales the others.  Against the oracle on a sample (1e-12 relative)."""
+    parts = [star_surface(29, seed=1), star_surface(11, seed=2)]
+    meshes = [dict(verts=v, tris=t, sigma=0.5 * triangle_diameters(v, t), targets=bbox_targets(v, m, pad=0.5, seed=m))
+              for (v, t), m in zip(parts, (66_000, 33_001))]
+    b = configs.concat_batch(meshes)
+    c = lss.Context()
+    c.set_options(far_field=lss.FAR_FMM, sigma_interp=1)
+    c.set_sources(b["verts"], b["tris"], dunavant6(), tri_offsets=b["tri_offsets"])
+    sig = c.eval_multiscale(b["targets"], 2.5, 0.07, x_mesh=b["target_mesh"])[2]
+    k = np.unique(np.linspace(0, len(sig) - 1, 300).astype(int))
+    want = oracle.sigma_field(b["verts"], b["tris"], b["targets"][k], 2.5, 0.07, tri_offsets=b["tri_offsets"],
+                              x_mesh=b["target_mesh"][k])
+    want = want[0] if isinstance(want, tuple) else want
+    assert np.abs(sig[k] / want - 1.0).max() <= 1e-12
