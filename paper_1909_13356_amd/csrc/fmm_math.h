@@ -178,8 +178,7 @@ LSS_HD void p2m_dipole(double rx, double ry, double rz, double ax, double ay, do
 //   dPhi/dz      = sum_{j, m>=0} w_m Re(L_{j+1}^m U_j^m)
 //   (dx + i dy)Phi = sum_{j, s} L_{j+1}^{s-1} U_j^s
 //                 = sum_{j, m>=0} L_{j+1}^{m-1} U_j^m - [m > 0] conj(L_{j+1}^{m+1} U_j^m)
-// l2p_sums leaves the unscaled sums: Phi = s[0], grad Phi = (s[1], s[2], s[3]) / side
-LSS_HD void l2p_sums(const double *L, double rx, double ry, double rz, int p, double s[4]) {
+LSS_HD void l2p(const double *L, double rx, double ry, double rz, double inv_s, int p, double &phi, double g[3]) {
     const double r2 = rx * rx + ry * ry + rz * rz;
     double ph = 0.0, gz = 0.0, Are = 0.0, Aim = 0.0;
     cd diag = {1.0, 0.0};
@@ -214,19 +213,10 @@ LSS_HD void l2p_sums(const double *L, double rx, double ry, double rz, int p, do
             }
         }
     }
-    s[0] = ph;
-    s[1] = Are;
-    s[2] = Aim;
-    s[3] = gz;
-}
-
-LSS_HD void l2p(const double *L, double rx, double ry, double rz, double inv_s, int p, double &phi, double g[3]) {
-    double s[4];
-    l2p_sums(L, rx, ry, rz, p, s);
-    phi = s[0];
-    g[0] = s[1] * inv_s;
-    g[1] = s[2] * inv_s;
-    g[2] = s[3] * inv_s;
+    phi = ph;
+    g[0] = Are * inv_s;
+    g[1] = Aim * inv_s;
+    g[2] = gz * inv_s;
 }
 
 // M2P: Phi and grad Phi of a multipole expansion M~ (real layout) of a box of
@@ -240,8 +230,7 @@ LSS_HD void l2p(const double *L, double rx, double ry, double rz, double inv_s, 
 // and in A the terms of M_n^{m'} with m' <= 0 are -conj(T_{n+1}^{|m'|+1} M_n^{|m'|}).
 // T_j^m is generated column by column (m = 0..p+1, j = m..p+1) and consumed at
 // once, as T_j^m M_j^m, T_j^m M_{j-1}^m, T_j^m M_{j-1}^{m+1} and -conj(T_j^m M_{j-1}^{m-1}).
-// m2p_sums leaves the unscaled sums: Phi = s[0] / s, grad Phi = (-s[1], s[2], -s[3]) / s^2
-LSS_HD void m2p_sums(const double *M, double rx, double ry, double rz, int p, double s[4]) {
+LSS_HD void m2p(const double *M, double rx, double ry, double rz, double inv_s, int p, double &phi, double g[3]) {
     const double r2 = rx * rx + ry * ry + rz * rz, ir2 = 1.0 / r2;
     double s0 = 0.0, s1 = 0.0, Are = 0.0, Aim = 0.0;
     cd diag = {sqrt(ir2), 0.0};
@@ -278,20 +267,11 @@ LSS_HD void m2p_sums(const double *M, double rx, double ry, double rz, int p, do
             }
         }
     }
-    s[0] = s0;
-    s[1] = Are;
-    s[2] = Aim;
-    s[3] = s1;
-}
-
-LSS_HD void m2p(const double *M, double rx, double ry, double rz, double inv_s, int p, double &phi, double g[3]) {
-    double s[4];
-    m2p_sums(M, rx, ry, rz, p, s);
     const double is2 = inv_s * inv_s;
-    phi = s[0] * inv_s;
-    g[0] = -s[1] * is2;
-    g[1] = s[2] * is2;
-    g[2] = -s[3] * is2;
+    phi = s0 * inv_s;
+    g[0] = -Are * is2;
+    g[1] = Aim * is2;
+    g[2] = -s1 * is2;
 }
 
 // Real-layout coefficient (n, m) as a complex number for any m in [-n, n]

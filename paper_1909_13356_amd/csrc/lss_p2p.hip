@@ -878,8 +878,8 @@ __device__ __forceinline__ void stage_local(const FmmEvalArgs &a, int32_t B, dou
     for (int k = threadIdx.x; k < a.ncp; k += blockDim.x) Ls[k] = src[k];
 }
 
-// M2P and L2P by a wave, one target per lane: the sums of fmm::m2p_sums and
-// fmm::l2p_sums, term by term in their order (the same result bit for bit),
+// M2P and L2P by a wave, one target per lane: the sums of fmm::m2p and
+// fmm::l2p before their scaling, term by term in their order (the same result bit for bit),
 // with what is the same for every term of a column taken out of it.  The
 // column's terms are split by the coefficients that they meet, so that a term
 // has no branch (there were five to eight); T's and U's factors are counted up
@@ -2604,8 +2604,8 @@ void launch_hess_tile(Ctx &c, unsigned grid, const FmmEvalArgs &a, double *hess)
     LSS_CHECK_LAUNCH("k_hess_fmm");
 }
 
-// nexp: expansions of a heavy tile evaluated at once (their buffers and
-// results fit the rings' LDS)
+// nexp: expansions of a heavy tile evaluated at once (their results fit the
+// rings' LDS)
 void launch_mixed_waves(Ctx &c, int64_t max_tiles, const FmmEvalArgs &a) {
     const size_t region = region_for(std::max(kMixedRingBytes, (kMixedWideBytes + kWide - 1) / kWide), 0);
     const int nexp = (int)std::min<size_t>(kWide, region * kWide / (sizeof(double) * 256));
@@ -2699,7 +2699,7 @@ void launch_eval_fmm(Ctx &c, int64_t max_tiles, const int32_t *ntiles_dev, const
         const size_t shm = sizeof(double) * (size_t)a.ncp;
         switch (fmm_tile(c)) {
             case 64: {
-                const size_t region = region_for(kChunkBytes, a.ncp);
+                const size_t region = region_for(kChunkBytes, 0);   // it stages no expansion
                 const int W = std::min(kHessWaves, waves_for(region));
                 hipLaunchKernelGGL(k_multiscale_waves, dim3(hess_grid(max_tiles, W)), dim3(64 * W), region * W, c.stream,
                                    a, *ms, (int)(region / sizeof(double)));
