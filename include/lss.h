@@ -160,9 +160,10 @@ typedef struct lss_stats {
                                  Newton step and compaction together) */
     int32_t pair_kernel_launches;  /* lss_eval: pair-kernel launches timed in pair_kernel_ms;
                                       lss_project: timed launches of Newton iterations (graphs of
-                                      4 iterations; with LSS_FAR_FMM the first iteration runs on
-                                      its own, and the active list is re-ordered by leaf after it
-                                      and after every 8 iterations) */
+                                      4 iterations, or of newton_max_iter where that is below 8
+                                      and not 4; with LSS_FAR_FMM the first iteration runs on its
+                                      own, and the active list is re-ordered by leaf after it and
+                                      after every min(newton_max_iter, 8) iterations) */
     int32_t pad0;
     double  lane_pairs;       /* pair evaluations the pair kernels spent, idle lanes of partly
                                  filled tiles included (last_pairs / lane_pairs = lane use) */

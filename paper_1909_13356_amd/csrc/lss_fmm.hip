@@ -6,19 +6,19 @@
 // on the FP64 matrix cores (v_mfma_f64_16x16x4f64).  M2M and L2L run one
 // launch per level.  M2L has two forms, both race free and deterministic:
 //   FP64 near fields (m2l_plan, m2l_pass; FP64 contexts and the
-//     target-attached width, whose 1e5 points on 43 200 triangles took 26.8 ms
-//     with the other form and 22.5 with this): all pairs sorted by operator, rotated
+//     target-attached width, whose 1e5 points on 43 200 triangles take 4 ms
+//     less of some 20 than with the other form): all pairs sorted by operator, rotated
 //     so that the operators split in two halves; one product launch and one
 //     sum launch per block of target boxes, each pair's product in a slot of
 //     its own and the sums in a fixed order.
 //   mixed contexts, and lists of 2^31 pairs and more: one launch per
 //     displacement class (one dense operator per class); inside a launch every
-//     destination box appears once.  The
-//     rotated form would change the far field by 1e-16, and a Newton iterate
+//     destination box appears once.  The rotated form would change the far field by 1e-16, and a Newton iterate
 //     moved by that makes a few FP32 pair sums of a million nodes round the
 //     other way (up to 7e-9 sigma in a node's h); the mixed projection is
-//     kept the same bit for bit.  What it would gain there is small: 1 to 3 ms
-//     of a 52 ms batch, nothing at 2e6 triangles.
+//     kept the same bit for bit.  What it gained there when it was tried is
+//     small: 1 to 3 ms of a batch of 24 surfaces (43 ms), nothing at 2e6
+//     triangles.
 #include <cstring>
 #include <algorithm>
 #include <hip/hip_runtime.h>

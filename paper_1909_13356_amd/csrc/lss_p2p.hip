@@ -1941,7 +1941,7 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(4)))
 // every target of the tile taking the folded far form (pair_hess_far), the
 // others pair_hess_cut, which still chooses per pair.  Bound by FP64 VALU
 // issue at three waves per SIMD (168 VGPRs).  2.9e5 chart nodes of 6348
-// triangles: 30 -> 12 ms (one wave per tile in grid order before).
+// triangles: 30 -> 11 ms (one wave per tile in grid order before).
 constexpr size_t kChunkBytes = 64 * (sizeof(Src) + sizeof(FarD));     // one staged chunk
 
 __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_hess_waves(
@@ -2052,7 +2052,7 @@ __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu
 // the cut of every target of the tile (the gap to the tile's bounding box
 // against the tile's largest sigma(x)) take the Laplace double layer, the
 // others pair_ms_cut, which still chooses per pair.  1e5 targets on 43 200
-// triangles: 19 -> 5.1 ms.
+// triangles: 19 -> 3.4 ms.
 __global__ __launch_bounds__(64 * kHessWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_multiscale_waves(
     FmmEvalArgs a, MsArgs ms, int region_doubles) {
     __shared__ WaveLds wl[kHessWaves];

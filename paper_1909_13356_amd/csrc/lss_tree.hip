@@ -597,15 +597,15 @@ __global__ void k_tile_bucket_count(int64_t max_tiles, const int32_t *__restrict
 // that single waves take end within that part of the launch of each other.
 //   Independent waves, 8 (FP64 evaluation; Hessian and sigma(x), which sum in
 // FP64 in mixed contexts too): nothing is lost on a heavy tile.  FP64
-// evaluation of 4e5 targets near a uniform sphere, and on a graded surface (ms):
-// 22.6, 11.8 at 8; 22.6, 13.5 at 4; 31.7, 13.8 at 2 (one wave per tile: 25.5,
-// 48.0).  Hessian at 2.9e5 chart nodes of 6348 triangles in an FP64 and in a
+// evaluation of 4e5 targets near a uniform sphere of 6912 triangles, and on a
+// graded surface of 31 212 (ms): 7.8, 13.7 at 8; 7.9, 17.4 at 4; 11.4, 15.3 at 2.
+// Hessian at 2.9e5 chart nodes of 6348 triangles in an FP64 and in a
 // mixed context, sigma(x) at 1e5 targets on 43 200 triangles in a mixed one:
 // 11.0, 7.7, 3.4 at 8; 11.0, 7.7, 3.7 at 4; 13.8, 9.0, 3.9 at 1.4.
 //   Waves in step, 1.4 (mixed evaluation): a heavy tile is 15% slower than single
-// waves where the chip is full anyway.  3e5 targets near the sphere, 8e5 on the
-// graded surface (ms): 6.9, 6.9 at 1.4; 6.7, 7.1 at 1; 7.9, 6.5 at 2 (one wave
-// per tile: 7.4, 21.2).
+// waves where the chip is full anyway.  3e5 targets near the sphere and on an
+// even surface of 43 200 triangles, 8e5 on the graded one (ms): 2.5, 2.9, 6.7
+// at 1.4; 2.4, 3.0, 6.6 at 1; 2.8, 3.4, 6.7 at 2; 2.6, 3.4, 8.6 at 8.
 constexpr double kShareApart = 8.0, kShareInStep = 1.4;
 __global__ __launch_bounds__(64) void k_tile_bucket_scan(int32_t *bucket, double line) {
     constexpr int kPer = kCostBuckets / 64;
