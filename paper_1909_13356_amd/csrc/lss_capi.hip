@@ -217,7 +217,7 @@ EvalBufs eval_bufs_ctx(Ctx &c, int64_t n) {
     b.sort_bytes = tb;
     b.part = nullptr;
     if (c.opt.far_field == LSS_FAR_DIRECT) {
-        c.part.ensure(direct_part_bytes(c, n));
+        ensure_direct_part(c, n);
         b.part = c.part.p;
     }
     b.pairs = c.pairs.as<double>();
@@ -413,7 +413,7 @@ void project(Ctx &c, const double *uv, int32_t np, double *h, double *xout, int8
     launch_chart_init(c, duv.as<double>(), np, N);
     ensure_targets(c, N);
     if (c.opt.far_field == LSS_FAR_FMM) ensure_tiles(c, N);
-    else c.part.ensure(direct_part_bytes(c, N));
+    else ensure_direct_part(c, N);
     NewtonState &s = c.ns;
     DBuf &phi = s.phi, &grad = s.grad;
     phi.ensure(sizeof(double) * N);

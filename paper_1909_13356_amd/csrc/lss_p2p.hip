@@ -2753,9 +2753,17 @@ int direct_splits(const Ctx &c, int64_t n) {
                          c.nmesh == 1);
 }
 
+// bytes of partial sums of one target and piece
+size_t direct_part_size(const Ctx &c) { return 8 * (c.opt.precision == LSS_MIXED ? sizeof(float) : sizeof(double)); }
+
 size_t direct_part_bytes(const Ctx &c, int64_t n) {
     const int s = direct_splits(c, n);
-    return s > 1 ? (size_t)n * (size_t)s * 8 * (c.opt.precision == LSS_MIXED ? sizeof(float) : sizeof(double)) : 0;
+    return s > 1 ? (size_t)n * (size_t)s * direct_part_size(c) : 0;
+}
+
+void ensure_direct_part(Ctx &c, int64_t n) {
+    if (direct_splits(c, n) > 1)
+        c.part.ensure((size_t)direct_most_partials(ceil_div(c.nnodes, direct_tile(c))) * direct_part_size(c));
 }
 
 void launch_p2p_direct(Ctx &c, int64_t n, const int32_t *n_dev, const double *tx, const double *ty,

@@ -38,6 +38,14 @@ inline int direct_pieces(int64_t tiles, int64_t chunks, int tile, bool whole) {
     return (int)((chunks + per - 1) / per);
 }
 
+// Targets times pieces of any call, at most: a context allocates for this once.
+// (The product rises and falls with the number of targets: with what a call
+// needs, one of fewer targets could need more than an earlier, larger one.)
+inline int64_t direct_most_partials(int64_t chunks) {
+    if (chunks <= 1) return 0;
+    return chunks < 4 ? chunks * 163840 : (int64_t)1 << 19;
+}
+
 // Piece k of the nodes [lo, hi), in whole chunks
 LSS_RULE void piece_range(int tile, int64_t k, int64_t pieces, int64_t &lo, int64_t &hi) {
     const int64_t chunks = (hi - lo + tile - 1) / tile;

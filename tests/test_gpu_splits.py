@@ -357,3 +357,24 @@ def test_sigma_field_pieces_of_several_runs():
                               x_mesh=b["target_mesh"][k])
     want = want[0] if isinstance(want, tuple) else want
     assert np.abs(sig[k] / want - 1.0).max() <= 1e-12
+
+
+@pytest.mark.parametrize("prec", [lss.FP64, lss.MIXED])
+def test_direct_workspace_holds_for_fewer_targets(prec):
+    """A direct sum's workspace is allocated once: calls of fewer targets, some of which have more targets times pieces
+    (104 000 in 5 against 110 000 in 4), take no more memory."""
+    torch = pytest.importorskip("torch")
+    v, t = cube_mesh(9)
+    x = torch.as_tensor(bbox_targets(v, 110_000, pad=0.5, seed=3), device="cuda")
+    phi, grad = torch.empty_like(x[:, 0].contiguous()), torch.empty_like(x)
+    c = lss.Context()
+    c.set_options(precision=prec)
+    c.set_sources(v, t, dunavant6())
+    c.set_sigma(0.1)
+    c.eval(x, phi=phi, grad=grad)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for n in (104_000, 80_000, 4096, 1):
+        c.eval(x[:n], phi=phi[:n], grad=grad[:n])
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] == free, n

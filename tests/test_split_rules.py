@@ -25,8 +25,8 @@ def test_m2l_plan_ends_where_its_indices_do(tmp_path):
 
 def test_every_piece_of_a_direct_sum_has_work(tmp_path):
     """All tile widths, target and node counts up to where the split ends: the pieces cover the nodes in order, none is
-    empty where a tile walks all nodes, and targets times pieces stay below 2^19 (the workspace of the allocation-free
-    call)."""
+    empty where a tile walks all nodes, and targets times pieces stay below what a context allocates for, 2^19 at most
+    (the workspace of the allocation-free call)."""
     assert _run(tmp_path, """
         for (int tile : {64, 128, 256})
             for (int64_t n = 1; n < 200000; n += 1 + n / 7)
@@ -41,7 +41,7 @@ def test_every_piece_of_a_direct_sum_has_work(tmp_path):
                             if (lo != at || hi < lo || (whole && hi == lo)) ++none;
                             at = hi;
                         }
-                        if (none || at != nodes || s < 1 || (s > 1 && n * s > (1 << 19))) {
+                        if (none || at != nodes || s < 1 || (s > 1 && n * s > direct_most_partials(chunks))) {
                             printf("%d %ld %ld: %d pieces, %ld wrong ", tile, (long)n, (long)nodes, s, (long)none);
                             return 0;
                         }
