@@ -889,9 +889,13 @@ __device__ __forceinline__ void stage_local(const FmmEvalArgs &a, int32_t B, dou
 // small tree a target meets as many terms as nodes: 24 ragged surfaces in mixed
 // precision 44.5 -> 42.5 ms, charts of 3e4 triangles in FP64 46.1 -> 43.9, a step
 // of 5e7 targets on 2e6 triangles 375 -> 368.
-//   FUSED: every product goes straight into its sum (12 operations a term in the
-// sums instead of 18, and the doubling of m > 0 taken out of them); for FP64
-// near fields.  Mixed ones keep the order of roundings (see the top of
+//   FUSED: every product goes straight into its column's sum (12 operations a
+// term in the sums instead of 18, and the doubling of m > 0 taken out of them),
+// and the columns' sums into the totals; for FP64 near fields.  A fused term
+// rounds its sum twice: with one running sum over all columns the rms error of
+// Phi was 4 to 10% above that of a rounding per term, with the columns apart it
+// is 2 to 9% below (charts and steps of 1728 to 2e5 triangles, against the
+// direct sum), at the same speed.  Mixed ones keep the order of roundings (see the top of
 // lss_fmm.hip on M2L).  The coefficients are the wave's own, so they are read
 // as scalars, where a read from LDS (8.7 cycles of it for two, three such a
 // term) kept it as busy as the VALU: the two changes 2e6 targets on 2e5
@@ -985,10 +989,14 @@ __device__ __forceinline__ void m2p_column(ColumnSums &q, Coef M, int m, int p, 
     m2p_term<FUSED, MM, true, false, true, true>(q, M, p + 1, m, w, rz, ir2);
 }
 
-// FUSED: the sums of m > 0 count twice, taken out of them by halving those of m = 0
-__device__ __forceinline__ void scale_values(ColumnSums &q, double f) {
-    q.s0 *= f;
-    q.s1 *= f;
+// FUSED: a column's sums into the totals (the values of m > 0 count twice), and cleared for the next
+__device__ __forceinline__ void add_column(ColumnSums &q, int m, double s[4]) {
+    const double w = m == 0 ? 1.0 : 2.0;
+    s[0] = fma(w, q.s0, s[0]);
+    s[1] += q.are;
+    s[2] += q.aim;
+    s[3] = fma(w, q.s1, s[3]);
+    q.s0 = q.s1 = q.are = q.aim = 0.0;
 }
 
 template <bool FUSED>
@@ -996,6 +1004,7 @@ __device__ __forceinline__ void wave_m2p_sums(Coef M, double rx, double ry, doub
     const double r2 = rx * rx + ry * ry + rz * rz, ir2 = 1.0 / r2;
     ColumnSums q;
     q.s0 = q.s1 = q.are = q.aim = 0.0;
+    if (FUSED) s[0] = s[1] = s[2] = s[3] = 0.0;
     fmm::cd diag = {sqrt(ir2), 0.0};
     for (int m = 0; m <= p + 1; ++m) {
         if (m > 0) diag = fmm::cscale(fmm::cmul(diag, fmm::cd{rx, ry}), -(2.0 * m - 1.0) * ir2);
@@ -1003,9 +1012,9 @@ __device__ __forceinline__ void wave_m2p_sums(Coef M, double rx, double ry, doub
         if (m == 0) m2p_column<FUSED, 0>(q, M, m, p, rz, ir2);
         else if (m == 1) m2p_column<FUSED, 1>(q, M, m, p, rz, ir2);
         else m2p_column<FUSED, 2>(q, M, m, p, rz, ir2);
-        if (FUSED && m == 0) scale_values(q, 0.5);
+        if (FUSED) add_column(q, m, s);
     }
-    if (FUSED) scale_values(q, 2.0);
+    if (FUSED) return;
     s[0] = q.s0;
     s[1] = q.are;
     s[2] = q.aim;
@@ -1063,6 +1072,7 @@ __device__ __forceinline__ void wave_l2p_sums(Coef L, double rx, double ry, doub
     const double r2 = rx * rx + ry * ry + rz * rz;
     ColumnSums q;
     q.s0 = q.s1 = q.are = q.aim = 0.0;
+    if (FUSED) s[0] = s[1] = s[2] = s[3] = 0.0;
     fmm::cd diag = {1.0, 0.0};
     for (int m = 0; m <= p; ++m) {
         if (m > 0) diag = fmm::cscale(fmm::cmul(diag, fmm::cd{rx, ry}), -0.5 / (double)m);
@@ -1070,9 +1080,9 @@ __device__ __forceinline__ void wave_l2p_sums(Coef L, double rx, double ry, doub
         if (m == 0) l2p_column<FUSED, 0>(q, L, m, p, rz, r2);
         else if (m == 1) l2p_column<FUSED, 1>(q, L, m, p, rz, r2);
         else l2p_column<FUSED, 2>(q, L, m, p, rz, r2);
-        if (FUSED && m == 0) scale_values(q, 0.5);
+        if (FUSED) add_column(q, m, s);
     }
-    if (FUSED) scale_values(q, 2.0);
+    if (FUSED) return;
     s[0] = q.s0;
     s[1] = q.are;
     s[2] = q.aim;

@@ -378,3 +378,21 @@ def test_direct_workspace_holds_for_fewer_targets(prec):
         c.eval(x[:n], phi=phi[:n], grad=grad[:n])
         torch.cuda.synchronize()
         assert torch.cuda.mem_get_info()[0] == free, n
+
+
+@pytest.mark.parametrize("n,seed", [(12, 1), (20, 1), (20, 3)])
+def test_expansion_sums_round_no_more_than_term_by_term(n, seed):
+    """FP64: the rms error of Phi against the direct sum with the expansions of the tile loop (products fused into a sum
+    per column) is no larger than with those of the 128-target tiles (one rounding per term).  The rest of the error is
+    the same; 0.5% for the order of the near sums."""
+    v, t = star_surface(n, seed=seed)
+    x = bbox_targets(v, 40_000, pad=0.05, seed=seed)
+    out = []
+    for kw in (dict(far_field=lss.FAR_DIRECT), dict(far_field=lss.FAR_FMM, tile=0), dict(far_field=lss.FAR_FMM, tile=128)):
+        c = lss.Context()
+        c.set_options(**kw)
+        c.set_sources(v, t, dunavant6())
+        c.set_sigma(0.5 * triangle_diameters(v, t))
+        out.append(c.eval(x)[0])
+    wave, fixed = (np.sqrt(((p - out[0]) ** 2).mean()) for p in out[1:])
+    assert wave <= 1.005 * fixed
