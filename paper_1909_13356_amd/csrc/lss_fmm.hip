@@ -1242,16 +1242,13 @@ void m2l_pass(Ctx &c, int p, int ncp) {
     }
     t.m2l_grp.ensure(4 * t.h_m2l_grp.size());
     LSS_HIP(hipMemcpyAsync(t.m2l_grp.p, t.h_m2l_grp.data(), 4 * t.h_m2l_grp.size(), hipMemcpyHostToDevice, c.stream));
-    // a launch takes a block, or as many as hold kM2LBytes of products together
+    // a launch takes as many blocks as the products of the fullest one hold
     const int nblk = (int)t.m2l_blk.size() - 1;
-    const int64_t together = (int64_t)(kM2LBytes / (16.0 * nqmax));
-    std::vector<int> cut{0};
     int64_t most = 0;
-    for (int b = 1; b <= nblk; ++b) {
-        if (b < nblk && t.m2l_blk[b + 1] - t.m2l_blk[cut.back()] <= together) continue;
-        most = std::max(most, t.m2l_blk[b] - t.m2l_blk[cut.back()]);
-        cut.push_back(b);
-    }
+    for (int b = 0; b < nblk; ++b) most = std::max(most, t.m2l_blk[b + 1] - t.m2l_blk[b]);
+    std::vector<int> cut{0};
+    for (int b = 1; b <= nblk; ++b)
+        if (b == nblk || t.m2l_blk[b + 1] - t.m2l_blk[cut.back()] > most) cut.push_back(b);
     t.m2l_y.ensure(sizeof(double2) * (size_t)most * rowmax);
     M2LArgs a;
     a.key = t.m2l_key2.as<uint64_t>();
