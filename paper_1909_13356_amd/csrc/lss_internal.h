@@ -373,7 +373,7 @@ void launch_gather_targets(Ctx &c, const double *x, const int32_t *x_mesh, const
 // part: direct_part_bytes of workspace (null: the node range is not split)
 int direct_splits(const Ctx &c, int64_t n);
 size_t direct_part_bytes(const Ctx &c, int64_t n);
-void ensure_direct_part(Ctx &c, int64_t n);   // the context's own, enough for every n
+void ensure_direct_part(Ctx &c, int64_t n);   // the context's own, enough for n and fewer targets
 void launch_p2p_direct(Ctx &c, int64_t n, const int32_t *n_dev, const double *tx, const double *ty,
                        const double *tz, const int32_t *tmesh, const int32_t *out_idx,
                        double *phi, double *grad, int grad_stride, double *pairs, void *part);

@@ -2772,8 +2772,8 @@ size_t direct_part_bytes(const Ctx &c, int64_t n) {
 }
 
 void ensure_direct_part(Ctx &c, int64_t n) {
-    if (direct_splits(c, n) > 1)
-        c.part.ensure((size_t)direct_most_partials(ceil_div(c.nnodes, direct_tile(c))) * direct_part_size(c));
+    const int tile = direct_tile(c);
+    c.part.ensure((size_t)direct_partials_kept(n, ceil_div(c.nnodes > 0 ? c.nnodes : 1, tile), tile) * direct_part_size(c));
 }
 
 void launch_p2p_direct(Ctx &c, int64_t n, const int32_t *n_dev, const double *tx, const double *ty,

@@ -38,12 +38,16 @@ inline int direct_pieces(int64_t tiles, int64_t chunks, int tile, bool whole) {
     return (int)((chunks + per - 1) / per);
 }
 
-// Targets times pieces of any call, at most: a context allocates for this once.
-// (The product rises and falls with the number of targets: with what a call
-// needs, one of fewer targets could need more than an earlier, larger one.)
-inline int64_t direct_most_partials(int64_t chunks) {
-    if (chunks <= 1) return 0;
-    return chunks < 4 ? chunks * 163840 : (int64_t)1 << 19;
+// Targets times pieces that a context allocates for on a call of n targets: what
+// the call needs while every chunk is a piece, else the most that any call can
+// need.  It does not fall as n grows (what a call needs does: 104 000 targets in
+// five pieces need more than 110 000 in four), so that a call of fewer targets
+// allocates nothing.
+inline int64_t direct_partials_kept(int64_t n, int64_t chunks, int tile) {
+    const int64_t full = (int64_t)2048 * (256 / tile), tiles = (n + tile - 1) / tile;
+    const int64_t most = chunks < 1024 ? chunks : 1024;
+    if (most <= 1 || tiles >= full * 5 / 16) return 0;
+    return full / tiles >= most ? n * most : (int64_t)1 << 19;
 }
 
 // Piece k of the nodes [lo, hi), in whole chunks

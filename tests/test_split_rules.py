@@ -41,10 +41,29 @@ def test_every_piece_of_a_direct_sum_has_work(tmp_path):
                             if (lo != at || hi < lo || (whole && hi == lo)) ++none;
                             at = hi;
                         }
-                        if (none || at != nodes || s < 1 || (s > 1 && n * s > direct_most_partials(chunks))) {
+                        if (none || at != nodes || s < 1 || (s > 1 && n * s > direct_partials_kept(n, chunks, tile))) {
                             printf("%d %ld %ld: %d pieces, %ld wrong ", tile, (long)n, (long)nodes, s, (long)none);
                             return 0;
                         }
                     }
+        printf("ok");
+    """) == ["ok"]
+
+
+def test_a_smaller_direct_sum_needs_no_more(tmp_path):
+    """What a context allocates for grows with the number of targets up to where the split ends, to 2^19 at most."""
+    assert _run(tmp_path, """
+        for (int tile : {64, 128, 256})
+            for (int64_t chunks = 1; chunks < 20000; chunks += 1 + chunks / 5) {
+                int64_t before = 0;
+                for (int64_t n = 1; n <= 163840 - tile; n += 1 + n / 50) {
+                    const int64_t k = direct_partials_kept(n, chunks, tile);
+                    if (k < before || k > (1 << 19)) {
+                        printf("%d %ld %ld: %ld after %ld ", tile, (long)chunks, (long)n, (long)k, (long)before);
+                        return 0;
+                    }
+                    before = k;
+                }
+            }
         printf("ok");
     """) == ["ok"]
